@@ -101,22 +101,22 @@ __device__ __forceinline__ void hllc3(real g, int a, const real (&UL)[5], const 
     const real SR = vmax(ul + cl, ur + cr);
     const real Ss = dv(pr - pl + rl * ul * (SL - ul) - rr * ur * (SR - ur), rl * (SL - ul) - rr * (SR - ur));
     const bool useL = Ss >= real(0);
-    const real rk = useL ? rl : rr, uk = useL ? ul : ur, vk = useL ? vl : vr, wk = useL ? wl : wr;
-    const real Ek = useL ? El : Er, pk = useL ? pl : pr, Sk = useL ? SL : SR, irk = useL ? irl : irr;
+    const bool takeL = SL >= real(0);
+    const bool takeStar = !takeL && (useL || SR > real(0));
+    // the side whose state the flux needs, in every branch (as in 2D)
+    const bool left = takeL || useL;
+    const real rk = left ? rl : rr, uk = left ? ul : ur, vk = left ? vl : vr, wk = left ? wl : wr;
+    const real Ek = left ? El : Er, pk = left ? pl : pr, Sk = left ? SL : SR, irk = left ? irl : irr;
     const real sku = Sk - uk;
     const real fac = dv(rk * sku, Sk - Ss);
     const real fk[5] = {rk * uk, rk * uk * uk + pk, rk * uk * vk, rk * uk * wk, uk * (Ek + pk)};
     const real uc[5] = {rk, rk * uk, rk * vk, rk * wk, Ek};
     const real us[5] = {fac, fac * Ss, fac * vk, fac * wk, fac * (Ek * irk + (Ss - uk) * (Ss + dv(pk, rk * sku)))};
-    const real fL[5] = {rl * ul, rl * ul * ul + pl, rl * ul * vl, rl * ul * wl, ul * (El + pl)};
-    const real fR[5] = {rr * ur, rr * ur * ur + pr, rr * ur * vr, rr * ur * wr, ur * (Er + pr)};
-    const bool takeL = SL >= real(0);
-    const bool takeStar = !takeL && (useL || SR > real(0));
     real f[5];
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
         const real fs = fk[m] + Sk * (us[m] - uc[m]);
-        f[m] = takeL ? fL[m] : (takeStar ? fs : fR[m]);
+        f[m] = takeStar ? fs : fk[m];
     }
     F[0] = f[0];
     F[4] = f[4];

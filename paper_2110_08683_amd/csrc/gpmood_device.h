@@ -366,23 +366,26 @@ __device__ __forceinline__ void hllc(real g, const real *UL, const real *UR, rea
     const real SR = vmax(ul + cl, ur + cr);
     const real Ss = dv(pr - pl + rl * ul * (SL - ul) - rr * ur * (SR - ur), rl * (SL - ul) - rr * (SR - ur));
     const bool useL = Ss >= real(0);
-    // star state of the side selected by the sign of S*
-    const real rk = useL ? rl : rr, uk = useL ? ul : ur, vk = useL ? vl : vr;
-    const real Ek = useL ? El : Er, pk = useL ? pl : pr, Sk = useL ? SL : SR, irk = useL ? irl : irr;
+    const bool takeL = SL >= real(0);
+    const bool takeStar = !takeL && (useL || SR > real(0));
+    // The flux needs one side only: outside the fan that side's own flux, inside it the
+    // star state of the side selected by the sign of S*.  (takeL || useL) names it in
+    // every branch, so the physical flux is formed once, on the selected state (forming
+    // both sides' and the star flux first took 28 more instructions a node: 2048^2 step
+    // 3.32 -> 3.25 ms in FP64, 3D 192^3 8.17 -> 8.07 ms in FP32).
+    const bool left = takeL || useL;
+    const real rk = left ? rl : rr, uk = left ? ul : ur, vk = left ? vl : vr;
+    const real Ek = left ? El : Er, pk = left ? pl : pr, Sk = left ? SL : SR, irk = left ? irl : irr;
     const real sku = Sk - uk;
     const real fac = dv(rk * sku, Sk - Ss);
     const real fk[4] = {rk * uk, rk * uk * uk + pk, rk * uk * vk, uk * (Ek + pk)};
     const real uc[4] = {rk, rk * uk, rk * vk, Ek};
     const real us[4] = {fac, fac * Ss, fac * vk, fac * (Ek * irk + (Ss - uk) * (Ss + dv(pk, rk * sku)))};
-    const real fL[4] = {rl * ul, rl * ul * ul + pl, rl * ul * vl, ul * (El + pl)};
-    const real fR[4] = {rr * ur, rr * ur * ur + pr, rr * ur * vr, ur * (Er + pr)};
-    const bool takeL = SL >= real(0);
-    const bool takeStar = !takeL && (useL || SR > real(0));
     real f[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const real fs = fk[k] + Sk * (us[k] - uc[k]);
-        f[k] = takeL ? fL[k] : (takeStar ? fs : fR[k]);
+        f[k] = takeStar ? fs : fk[k];
     }
     F[0] = f[0];
     F[n] = f[1];
