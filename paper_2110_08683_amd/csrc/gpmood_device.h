@@ -229,12 +229,23 @@ __device__ __forceinline__ real node_weight(const Weights<real> &W, int k)
 template <typename T>
 using cptr = const __attribute__((address_space(4))) T *;
 
+// The radius-R reconstruction weights [direction][slot][entry] of W, in the constant
+// address space.
 template <int R, typename real>
-__device__ __forceinline__ real wq(const Weights<real> &W, int dir, int slot, int e)
+__device__ __forceinline__ cptr<real> weight_table(cptr<Weights<real>> W)
 {
-    if constexpr (R == 3) return W.w3[dir][slot][e];
-    else if constexpr (R == 2) return W.w2[dir][slot][e];
-    else return W.w1[dir][0][e];
+    if constexpr (R == 3) return &W->w3[0][0][0];
+    else if constexpr (R == 2) return &W->w2[0][0][0];
+    else return &W->w1[0][0][0];
+}
+
+// The same pointer, as one the compiler takes for a new one: what is read through it
+// is read (by scalar loads) where it is used, not once ahead of a loop.
+template <typename T>
+__device__ __forceinline__ cptr<T> reread(cptr<T> p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 // The four parity sums of the mirror cells pp = (+a,+b), mp = (-a,+b),
@@ -261,32 +272,6 @@ __device__ __forceinline__ real axis_sum(real x, real y)
     return x + y;
 }
 
-// Parity sums Q[e] of one variable's radius-R stencil values; ld(di, dj) returns
-// the cell average at offset (di, dj).
-template <int R, typename real, typename Load>
-__device__ __forceinline__ void build_Q(real (&Q)[kNQ[R]], Load ld)
-{
-#pragma unroll
-    for (int e = 0; e < kNQ[R]; ++e) {
-        const int a = kQ[e].a, b = kQ[e].b, c = kQ[e].comp;
-        if (a == 0 && b == 0) {
-            Q[e] = ld(0, 0);
-        } else if (b == 0) {
-            if (c == C_EE) Q[e] = ld(a, 0) + ld(-a, 0);
-            else Q[e] = ld(a, 0) - ld(-a, 0);
-        } else if (a == 0) {
-            if (c == C_EE) Q[e] = ld(0, b) + ld(0, -b);
-            else Q[e] = ld(0, b) - ld(0, -b);
-        } else {
-            // four entries per (a, b): EE, OE, EO, OO in that order (see kQ)
-            if (c == C_EE) {
-                const real pp = ld(a, b), mp = ld(-a, b), pm = ld(a, -b), mm = ld(-a, -b);
-                parity_sums(pp, mp, pm, mm, Q[e], Q[e + 1], Q[e + 2], Q[e + 3]);
-            }
-        }
-    }
-}
-
 // Index of the transposed entry (b, a) of kQ entry e, with OE and EO exchanged.
 constexpr int transposed_entry(int e)
 {
@@ -296,37 +281,132 @@ constexpr int transposed_entry(int e)
     return -1;
 }
 
-// The 2q face states of one variable for direction DIR (0: x faces, 1: y faces):
-// sm[k] on the - face, sp[k] on the + face, node k in table order.  ISO: the grid
-// is isotropic (equal spacing and length scale, so the y weights are exactly the
-// transposed x weights) and a y face computes what an x face computes on the
-// transposed grid: x weight e times the transposed entry, accumulated in the x
-// faces' order, so both axes round alike.  Without ISO the y weights are read at
-// the transposed entry in the same order (the same bits when they are isotropic).
-template <int R, int DIR, bool ISO = false, typename real>
-__device__ __forceinline__ void states_dir(const real (&Q)[kNQ[R]], const Weights<real> &W,
-                                           real (&sm)[nodes_of(R)], real (&sp)[nodes_of(R)])
+// First and last + 1 entry of position group GRP of kQ: the positions come in groups
+// closed under the exchange of the axes, {(0,0)}, {(1,0), (0,1)}, {(2,0), (0,2)},
+// {(1,1)}, {(3,0), (0,3)}, {(2,1), (1,2)}.
+constexpr int kGroup[7] = {0, 1, 5, 9, 13, 17, 25};
+constexpr int groups_of(int R) { return R == 1 ? 2 : (R == 2 ? 4 : 6); }
+
+// Accumulators of one variable's face states in the directions D0 .. D1 - 1 (0: x
+// faces, 1: y faces): [direction - D0][slot][component].
+template <int R, int D0, int D1, typename real>
+struct StateAcc {
+    real p[D1 - D0][slots_of(R)][4];
+};
+
+// One position group's share of the face states of one variable; ld(di, dj) returns
+// the cell average at an offset.  w holds the group's weights [direction][slot][entry].
+// ISO: the grid is isotropic (equal spacing and length scale, so the y weights are
+// exactly the transposed x weights) and a y face computes what an x face computes on
+// the transposed grid: x weight e times the transposed entry, accumulated in the x
+// faces' order, so both axes round alike.  Without ISO the y weights are read at the
+// transposed entry in the same order (the same bits when they are isotropic).
+template <int R, int GRP, bool ISO, int D0, int D1, typename real, typename Load>
+__device__ __forceinline__ void add_group(StateAcc<R, D0, D1, real> &acc, const real (&w)[ISO ? 1 : D1 - D0][slots_of(R)][8],
+                                          Load ld)
+{
+    constexpr int e0 = kGroup[GRP], e1 = kGroup[GRP + 1];
+    real Q[e1 - e0];
+#pragma unroll
+    for (int e = e0; e < e1; ++e) {
+        const int a = kQ[e].a, b = kQ[e].b, c = kQ[e].comp, k = e - e0;
+        if (a == 0 && b == 0) {
+            Q[k] = ld(0, 0);
+        } else if (b == 0) {
+            Q[k] = c == C_EE ? ld(a, 0) + ld(-a, 0) : ld(a, 0) - ld(-a, 0);
+        } else if (a == 0) {
+            Q[k] = c == C_EE ? ld(0, b) + ld(0, -b) : ld(0, b) - ld(0, -b);
+        } else if (c == C_EE) {
+            // four entries per (a, b): EE, OE, EO, OO in that order (see kQ)
+            parity_sums(ld(a, b), ld(-a, b), ld(a, -b), ld(-a, -b), Q[k], Q[k + 1], Q[k + 2], Q[k + 3]);
+        }
+    }
+#pragma unroll
+    for (int dir = D0; dir < D1; ++dir) {
+        const int cN = dir == 0 ? C_EO : C_OE;  // odd along the face (node sign)
+#pragma unroll
+        for (int p = 0; p < slots_of(R); ++p)
+#pragma unroll
+            for (int e = e0; e < e1; ++e) {
+                const int et = dir == 1 ? transposed_entry(e) : e, c = kQ[et].comp;
+                // the centre node does not use its odd-along-the-face entries
+                if (slot_is_zero(R, p) && (c == cN || c == C_OO)) continue;
+                const real we = w[ISO ? 0 : dir - D0][p][(ISO ? e : et) - e0];
+                acc.p[dir - D0][p][c] = fma(we, Q[et - e0], acc.p[dir - D0][p][c]);
+            }
+    }
+}
+
+// The group's weights from the table wt (weight_table<R>), by scalar loads.
+template <int R, int GRP, bool ISO, int D0, int D1, typename real>
+__device__ __forceinline__ void load_group(cptr<real> wt, real (&w)[ISO ? 1 : D1 - D0][slots_of(R)][8])
+{
+    constexpr int e0 = kGroup[GRP], e1 = kGroup[GRP + 1];
+#pragma unroll
+    for (int d = 0; d < (ISO ? 1 : D1 - D0); ++d)
+#pragma unroll
+        for (int p = 0; p < slots_of(R); ++p)
+#pragma unroll
+            for (int e = e0; e < e1; ++e) w[d][p][e - e0] = wt[((ISO ? 0 : D0 + d) * slots_of(R) + p) * kNQ[R] + e];
+}
+
+// These values are formed here: not put off to where they are used, with everything
+// they are made of in registers until then.
+template <typename real>
+__device__ __forceinline__ void hold4(real (&x)[4])
+{
+    asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+}
+
+// Accumulators of all four variables, group by group; ld(v, di, dj).  A group's
+// weights are read once for the four variables and both directions (128 products of
+// the widest group's 16 weights) and given up before the next group's are read: held
+// for a whole row they do not fit the scalar registers, and every product then first
+// fetches its weight from the vector register it was put aside in.
+template <int R, bool ISO, int GRP = 0, int D0, int D1, typename real, typename Load>
+__device__ __forceinline__ void accumulate(StateAcc<R, D0, D1, real> (&acc)[4], cptr<real> wt, Load ld)
+{
+    if constexpr (GRP == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int d = 0; d < D1 - D0; ++d)
+#pragma unroll
+                for (int p = 0; p < slots_of(R); ++p)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[v].p[d][p][c] = real(0);
+    }
+    if constexpr (GRP < groups_of(R)) {
+        real w[ISO ? 1 : D1 - D0][slots_of(R)][8];
+        load_group<R, GRP, ISO, D0, D1>(reread(wt), w);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            add_group<R, GRP, ISO>(acc[v], w, [&](int di, int dj) { return ld(v, di, dj); });
+#pragma unroll
+            for (int d = 0; d < D1 - D0; ++d)
+#pragma unroll
+                for (int p = 0; p < slots_of(R); ++p) hold4(acc[v].p[d][p]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate<R, ISO, GRP + 1>(acc, wt, ld);
+    }
+}
+
+// The q states of one variable on the - face (sm) and the + face (sp) of direction
+// DIR (0: x faces, 1: y faces), node k in table order.
+template <int R, int DIR, int D0, int D1, typename real>
+__device__ __forceinline__ void states_of(const StateAcc<R, D0, D1, real> &acc, real (&sm)[nodes_of(R)],
+                                          real (&sp)[nodes_of(R)])
 {
     constexpr int q = nodes_of(R);
     constexpr int cF = DIR == 0 ? C_OE : C_EO;  // odd across the face
     constexpr int cN = DIR == 0 ? C_EO : C_OE;  // odd along the face (node sign)
 #pragma unroll
     for (int p = 0; p < slots_of(R); ++p) {
-        real P[4] = {real(0), real(0), real(0), real(0)};
-        const bool zero = slot_is_zero(R, p);
-#pragma unroll
-        for (int e = 0; e < kNQ[R]; ++e) {
-            // y faces take the entries in the transposed order in both builds, so an
-            // isotropic grid gives the same bits whichever build runs it
-            const int et = DIR == 1 ? transposed_entry(e) : e;
-            const int c = kQ[et].comp;
-            if (zero && (c == cN || c == C_OO)) continue;
-            const real w = DIR == 0 ? wq<R>(W, 0, p, e) : (ISO ? wq<R>(W, 0, p, e) : wq<R>(W, 1, p, et));
-            P[c] = fma(w, Q[et], P[c]);
-        }
+        const real(&P)[4] = acc.p[DIR - D0][p];
         const real A = P[C_EE] + P[cF];
         const real Bm = P[C_EE] - P[cF];
-        if (zero) {
+        if (slot_is_zero(R, p)) {
             sp[p] = A;
             sm[p] = Bm;
         } else {
@@ -340,7 +420,7 @@ __device__ __forceinline__ void states_dir(const real (&Q)[kNQ[R]], const Weight
     }
 }
 
-// Parity sums of the four mirror cells (+-a, +-b) of one variable, as in build_Q.
+// Parity sums of the four mirror cells (+-a, +-b) of one variable.
 template <typename real>
 __device__ __forceinline__ void parity4(real pp, real mp, real pm, real mm, real (&Q)[4])
 {
@@ -458,6 +538,28 @@ __device__ __forceinline__ int lane_here()
     int l;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
     return l;
+}
+
+// The value of the next (OFF = +1) or previous (OFF = -1) lane of the wavefront, by a
+// data-parallel shift: one vector move per 32 bits, with no LDS round trip.  Lane 63
+// (lane 0) gets zero.
+template <int OFF>
+__device__ __forceinline__ int lane_shift(int x)
+{
+    static_assert(OFF == 1 || OFF == -1, "one lane");
+    return __builtin_amdgcn_update_dpp(0, x, OFF == 1 ? 0x130 : 0x138, 0xf, 0xf, true);  // wave_shl:1, wave_shr:1
+}
+template <int OFF>
+__device__ __forceinline__ float lane_shift(float x)
+{
+    return __builtin_bit_cast(float, lane_shift<OFF>(__builtin_bit_cast(int, x)));
+}
+template <int OFF>
+__device__ __forceinline__ double lane_shift(double x)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)lane_shift<OFF>((int)(unsigned)b), hi = (unsigned)lane_shift<OFF>((int)(unsigned)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
 // A value the whole wavefront holds, made scalar.

@@ -113,11 +113,10 @@ __device__ __forceinline__ void claim_after_lowering(const StageArgs<real> &A, c
 // made after the pass (k_claims_first, or k_claims_first_batch in a batch), which keeps
 // the claim atomics, and the wait for their results, out of the march.
 template <typename real, int RT, bool ISO, bool HLL, bool BND>
-__device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const PassOut &P, int wid,
-                                                real (*ring)[4][LW])
+__device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const PassOut &P, cptr<Weights<real>> W,
+                                                int wid, real (*ring)[4][LW])
 {
     constexpr int q = nodes_of(RT);
-    constexpr int NQ = kNQ[RT];
     const int lane = threadIdx.x & 63;
 
     const int nx = A.nx, ny = A.ny, T = A.rows;
@@ -129,56 +128,73 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
     const int i = x0 - 1 + lane;
     const bool own_col = lane >= 1 && lane <= 62 && i < nx;
     const bool own = own_col;
+    const cptr<real> wtab = weight_table<RT>(W);
     const size_t plane = (size_t)nx * ny;
     const size_t nfx = (size_t)(nx + 1) * ny, nfy = (size_t)nx * (ny + 1);
 
+    // A ring row: columns x0 - 4 .. x0 + 65.  Lane l loads column l of every variable;
+    // the six columns left over are loaded by lanes 0..23 together, lane 6 v + k taking
+    // column 64 + k of variable v.
     const int sc0 = remap(x0 - 4 + lane, nx, A.bcx);
-    const bool has1 = lane < LW - 64;
-    const int sc1 = remap(x0 - 4 + 64 + (has1 ? lane : 0), nx, A.bcx);
+    const bool has1 = lane < 4 * (LW - 64);
+    const int ev = lane / (LW - 64), ec = 64 + lane % (LW - 64);
+    const size_t eo = has1 ? ev * plane + remap(x0 - 4 + ec, nx, A.bcx) : sc0;
     const real *__restrict__ Us = A.Us;
-
-    auto load_row = [&](int jr, real (&pf)[4][2]) {
-        const size_t rowoff = (size_t)remap(jr, ny, A.bcy) * nx;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            pf[v][0] = Us[v * plane + rowoff + sc0];
-            pf[v][1] = has1 ? Us[v * plane + rowoff + sc1] : real(0);
+    // source row of ring row jr (-4 <= jr <= ny + 4: at most two periods of 4 rows away)
+    auto src_row = [&](int jr) {
+        if (A.bcy == 0) {
+            int r = jr < 0 ? jr + ny : jr;
+            r = r >= ny ? r - ny : r;
+            return r >= ny ? r - ny : r;
         }
+        if (BND && A.bcy == 2) jr = jr < 0 ? -1 - jr : (jr >= ny ? 2 * ny - 1 - jr : jr);
+        return jr < 0 ? 0 : (jr >= ny ? ny - 1 : jr);
+    };
+    struct Row {
+        real c[4], e;
+    };
+    auto load_row = [&](int jr, Row &pf) {
+        const size_t rowoff = (size_t)src_row(jr) * nx;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pf.c[v] = Us[v * plane + rowoff + sc0];
+        pf.e = Us[rowoff + eo];
     };
     // Reflecting walls reverse the x momentum of mirrored columns and the y
     // momentum of mirrored rows; applied here, not at the load, which stays in flight.
-    auto store_row = [&](int jr, real (&pf)[4][2]) {
+    auto store_row = [&](int jr, Row &pf) {
         const int slot = jr & 7;
         // (BND: the build for grids with a reflecting axis or an inflow slit)
         if (BND && A.bcx == 2) {
-            const int c0 = x0 - 4 + lane, c1 = c0 + 64;
-            if (c0 < 0 || c0 >= nx) pf[1][0] = -pf[1][0];
-            if (c1 >= nx) pf[1][1] = -pf[1][1];
+            const int c0 = x0 - 4 + lane, c1 = x0 - 4 + ec;
+            if (c0 < 0 || c0 >= nx) pf.c[1] = -pf.c[1];
+            if (ev == 1 && c1 >= nx) pf.e = -pf.e;
         }
         if (BND && A.bcy == 2 && (jr < 0 || jr >= ny)) {
-            pf[2][0] = -pf[2][0];
-            pf[2][1] = -pf[2][1];
+            pf.c[2] = -pf.c[2];
+            if (ev == 2) pf.e = -pf.e;
         }
         if (BND && A.slit && (((A.slit & 1) && jr < 0) || ((A.slit & 2) && jr >= ny))) {
             // ghost rows of an inflow slit hold the injected state
-            const int c0 = x0 - 4 + lane, c1 = c0 + 64;
+            const int c0 = x0 - 4 + lane, c1 = x0 - 4 + ec;
             const int side = jr < 0 ? 0 : 1;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                if (c0 >= A.si0 && c0 < A.si1) pf[v][0] = A.slitU[side][v];
-                if (c1 >= A.si0 && c1 < A.si1) pf[v][1] = A.slitU[side][v];
+                if (c0 >= A.si0 && c0 < A.si1) pf.c[v] = A.slitU[side][v];
+                if (ev == v && c1 >= A.si0 && c1 < A.si1) pf.e = A.slitU[side][v];
             }
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            ring[slot][v][lane] = pf[v][0];
-            if (has1) ring[slot][v][64 + lane] = pf[v][1];
-        }
+        for (int v = 0; v < 4; ++v) ring[slot][v][lane] = pf.c[v];
+        if (has1) ring[slot][ev][ec] = pf.e;
     };
-    for (int jr = y0 - 4; jr <= y0 + 2; ++jr) {
-        real pf[4][2];
-        load_row(jr, pf);
-        store_row(jr, pf);
+    {
+        // the first seven rows, all loads in flight together
+        Row pf[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) load_row(y0 - 4 + r, pf[r]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 7; ++r) store_row(y0 - 4 + r, pf[r]);
     }
     wave_lds_sync();
 
@@ -193,45 +209,39 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
     for (int v = 0; v < 4; ++v) { Gprev[v] = real(0); dFxP[v] = real(0); }
 
     for (int j = y0 - 1; j <= yend; ++j) {
-        // U^n of the cell this row completes, (i, j-1), issued before the row
-        // prefetch: waiting for it later leaves the prefetch in flight
-        real unp[4] = {real(0), real(0), real(0), real(0)};
-        if (A.s != 0 && own && j - 1 >= y0) {
-            const unsigned c = (unsigned)(j - 1) * (unsigned)nx + (unsigned)(x0 - 1 + lane_here());
-#pragma unroll
-            for (int v = 0; v < 4; ++v) unp[v] = (A.Un + v * plane)[c];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        real pf[4][2];
+        Row pf;
         load_row(j + 4, pf);  // in flight during this row's arithmetic
         const bool doX = j >= y0 && j < yend;
         const bool first = j == y0 - 1;
 
-        real sxm[q][4], sxp[q][4], sym[q][4], syp[q][4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            real Q[NQ];
-            build_Q<RT>(Q, [&](int di, int dj) { return ring[(j + dj) & 7][v][lane + 3 + di]; });
-            real m_[q], p_[q];
-            // x states also on the two rows that do not use them: no branch here
-            states_dir<RT, 0, ISO>(Q, A.W, m_, p_);
-#pragma unroll
-            for (int k = 0; k < q; ++k) { sxm[k][v] = m_[k]; sxp[k][v] = p_[k]; }
-            states_dir<RT, 1, ISO>(Q, A.W, m_, p_);
-#pragma unroll
-            for (int k = 0; k < q; ++k) { sym[k][v] = m_[k]; syp[k][v] = p_[k]; }
-        }
-
+        // The x faces, then the y faces: half of the accumulators and states are live at
+        // a time.  Each reads the ring through a lane index the compiler takes for a new
+        // one, so that the ring's values, and their sums, are read and formed again (8%
+        // more instructions) instead of staying in registers in between.
         real dFx[4] = {real(0), real(0), real(0), real(0)};
         bool rsx = false;
         if (doX) {
+            real sxm[q][4], sxp[q][4];
+            {
+                int lx = lane;
+                asm volatile("" : "+v"(lx));
+                StateAcc<RT, 0, 1, real> acc[4];
+                accumulate<RT, ISO>(acc, wtab, [&](int v, int di, int dj) { return ring[(j + dj) & 7][v][lx + 3 + di]; });
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    real m_[q], p_[q];
+                    states_of<RT, 0>(acc[v], m_, p_);
+#pragma unroll
+                    for (int k = 0; k < q; ++k) { sxm[k][v] = m_[k]; sxp[k][v] = p_[k]; }
+                }
+            }
             real F[4] = {real(0), real(0), real(0), real(0)};
             bool badNb = false;
 #pragma unroll
             for (int k = 0; k < q; ++k) {
                 real ur[4], f[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) ur[v] = __shfl_down(sxm[k][v], 1);
+                for (int v = 0; v < 4; ++v) ur[v] = lane_shift<1>(sxm[k][v]);
                 bool bl, br;
                 riemann<0, HLL>(g, sxp[k], ur, f, bl, br);
                 rsx = rsx || bl;
@@ -239,6 +249,7 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
                 const real w = node_weight<RT>(A.W, k);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) F[v] = fma(w, f[v], F[v]);
+                hold4(F);  // one node after the other
             }
             // store face i+1/2: lanes of the strip's own cells, plus the domain's left face
             if ((own || (lane == 0 && x0 == 0)) && j < ny) {
@@ -251,18 +262,41 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
             // an inadmissible state on either side of the face troubles both of its
             // cells: this lane's cell takes faces i+1/2 and i-1/2 (the lane below's)
             const bool fbad = rsx || badNb;
-            const int badm = __shfl_up((int)fbad, 1);
+            const int badm = lane_shift<-1>((int)fbad);
             rsx = fbad || (badm != 0);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) dFx[v] = F[v] - __shfl_up(F[v], 1);
+            for (int v = 0; v < 4; ++v) dFx[v] = F[v] - lane_shift<-1>(F[v]);
+        }
+
+        real sym[q][4], syp[q][4];
+        {
+            int ly = lane;
+            asm volatile("" : "+v"(ly));
+            StateAcc<RT, 1, 2, real> acc[4];
+            accumulate<RT, ISO>(acc, wtab, [&](int v, int di, int dj) { return ring[(j + dj) & 7][v][ly + 3 + di]; });
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                real m_[q], p_[q];
+                states_of<RT, 1>(acc[v], m_, p_);
+#pragma unroll
+                for (int k = 0; k < q; ++k) { sym[k][v] = m_[k]; syp[k][v] = p_[k]; }
+            }
         }
 
         if (!first) {
             real G[4] = {real(0), real(0), real(0), real(0)};
             bool badLy = false, badRy = false;
+            real unp[4] = {real(0), real(0), real(0), real(0)};
             real fh[q / 2 > 0 ? q / 2 : 1][4];  // HLL builds: fluxes of nodes 0 .. q/2-1, paired below
 #pragma unroll
             for (int k = 0; k < q; ++k) {
+                if (k == q - 1 && A.s != 0 && own && j - 1 >= y0) {
+                    // U^n of the cell this row completes, (i, j-1): issued once the
+                    // other nodes' states are given up, in flight during this node
+                    const unsigned c = (unsigned)(j - 1) * (unsigned)nx + (unsigned)(x0 - 1 + lane_here());
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) unp[v] = (A.Un + v * plane)[c];
+                }
                 real f[4];
                 bool bl, br;
                 riemann<1, HLL>(g, sypP[k], sym[k], f, bl, br);
@@ -286,6 +320,7 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
                 } else {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) G[v] = fma(w, f[v], G[v]);
+                    hold4(G);
                 }
             }
             // store face j-1/2 (y index j): the segment's faces above its first row,
@@ -346,12 +381,28 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
     }
 }
 
+// Bound by vector instruction issue: a row of a march is about 2300 vector instructions
+// in FP32 and 3400 in FP64 (divisions and square roots are sequences there), against
+// 48 and 96 bytes of memory per cell.  So the kernel keeps its instructions to the
+// arithmetic and its registers to what lets several marches share a SIMD: 118 vector
+// registers in FP32 (four marches), 231 in FP64 (two), nothing spilled.  What that took:
+// the weights are read again for every position group (add_group) instead of held in
+// scalar registers, which do not hold them all and had every product preceded by a move
+// from a spilled one; the row index is scalar; the x faces are finished before the y
+// faces begin; sums and node fluxes are formed where they stand (hold4); neighbours'
+// states come by lane shifts.  2048^2: 778 -> 502 us a launch in FP64, 301 -> 213 us in
+// FP32 (8-row marches), against 5778 -> 3463 and 3152 -> 2354 vector instructions.
 template <typename real, int RT, int WPB, bool ISO, bool HLL, bool BND>
-__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 2 : 1) void k_first_pass(const StageArgs<real> A, const PassOut P)
+__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 4 : 2) void k_first_pass(const StageArgs<real>, const PassOut P)
 {
     __shared__ real ring_all[WPB][8][4][LW];
-    const int wv = threadIdx.x >> 6;
-    first_pass_wave<real, RT, ISO, HLL, BND>(A, P, xcd_tile(blockIdx.x, gridDim.x) * WPB + wv, ring_all[wv]);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // the march's rows are scalar
+    // the first argument where it lies in the kernel's argument block: read through this
+    // pointer a value is fetched again (a scalar load) rather than kept in a register
+    // from the kernel's entry on
+    const cptr<StageArgs<real>> A = (cptr<StageArgs<real>>)__builtin_amdgcn_kernarg_segment_ptr();
+    first_pass_wave<real, RT, ISO, HLL, BND>(*(const StageArgs<real> *)A, P, &A->W,
+                                             xcd_tile(blockIdx.x, gridDim.x) * WPB + wv, ring_all[wv]);
 }
 
 // The claims of the cells the first pass lowered (listed in low, count *nlow):
@@ -1252,7 +1303,7 @@ __device__ __forceinline__ int find_problem(cptr<int> prefix, int n, int b)
 }
 
 template <typename real, int RT, int WPB, bool ISO, bool HLL, bool BND>
-__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 2 : 1) void k_first_pass_batch(const BatchTabs<real> B)
+__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 4 : 2) void k_first_pass_batch(const BatchTabs<real> B)
 {
     __shared__ real ring_all[WPB][8][4][LW];
     cptr<int> blk = (cptr<int>)B.blk;
@@ -1263,8 +1314,9 @@ __global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 2 : 1) void k_first_p
     // lowered cells are listed in clist[0]; k_claims_first_batch makes their claims
     Q.clist = C.clist[0];
     Q.ccount = &C.ctl->nlow;
-    const int wv = threadIdx.x >> 6;
-    first_pass_wave<real, RT, ISO, HLL, BND>(A, Q, (blockIdx.x - blk[p]) * WPB + wv, ring_all[wv]);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    first_pass_wave<real, RT, ISO, HLL, BND>(A, Q, &(((cptr<StageArgs<real>>)B.args) + p)->W,
+                                             (blockIdx.x - blk[p]) * WPB + wv, ring_all[wv]);
 }
 
 // Multi-block cascade passes of a batch.  Before each pass, k_batch_plan sizes
