@@ -233,8 +233,9 @@ gpm_status gpm_totals_static(gpm_ctx *ctx, const void *U, double totals[4]);
    pass leaves more than 4 x tail_threshold), with one host check per batch.
    passes_per_check (1..128) is the smallest batch; the batch otherwise follows
    the previous stage's number of multi-block passes.  rows_per_wave (4..256):
-   rows per wavefront march in the first pass.  Defaults 4, 12 (24 in FP64 when
-   the grid has at least 2048 marches of 24 rows) and 32. */
+   rows per wavefront march in the first pass.  Defaults 4, a length chosen from
+   the grid and the precision (1 to 12 rows: short marches where the grid has too
+   few of them to fill the GPU) and 32. */
 gpm_status gpm_set_tuning(gpm_ctx *ctx, int passes_per_check, int rows_per_wave, int tail_threshold);
 
 /* Instrumentation for measurement (not part of the method).  mode bit 0: every
@@ -338,7 +339,8 @@ gpm_status gpm_batch_workspace_size(const gpm_batch *b, size_t *bytes);
    clears it.  Synchronising.  Errors: GPM_EINVAL for NULL or misalignment. */
 gpm_status gpm_batch_bind(gpm_batch *b, void *mem);
 
-/* First-pass rows per wavefront for every problem (4..256, default 12). */
+/* First-pass rows per wavefront for every problem (4..256; the default is chosen
+   from the whole batch, as for a single problem). */
 gpm_status gpm_batch_set_tuning(gpm_batch *b, int rows_per_wave);
 
 /* First-pass rows per wavefront of each problem (nprob values, 4..256). */

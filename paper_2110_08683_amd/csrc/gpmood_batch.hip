@@ -22,15 +22,7 @@
 
 namespace {
 
-// First-pass block count of one problem (strips of 62 columns x `rows` rows,
-// WPB wavefronts per block) and dt blocks (256 threads, up to 16 cells each).
-int fp_blocks(const gpm_ctx *c, int rows)
-{
-    const int wpb = c->prec == GPM_F64 ? 2 : 4;
-    const int waves = ((c->nx + 61) / 62) * ((c->ny + rows - 1) / rows);
-    return (waves + wpb - 1) / wpb;
-}
-
+// Blocks of the dt reduction of one problem (256 threads, up to 16 cells each).
 int dt_blocks(const gpm_ctx *c)
 {
     const size_t b = (c->ncell + 4095) / 4096;
@@ -47,7 +39,7 @@ struct gpm_batch {
     std::vector<gpm_ctx *> ctx;
     bool have_scheme = false;
     char *mem = nullptr;
-    int rows = 12;
+    int rows = 0;               // first-pass rows per wavefront (0: march_rows over the whole batch)
     std::vector<int> prow;      // first-pass rows per wavefront of each problem (empty: rows)
     int cur = 0;  // slot rotation of the next step (the same for every problem)
     // device tables (inside the caller buffer)
@@ -122,6 +114,18 @@ static BatchLayout batch_layout(const gpm_batch *b)
     return L;
 }
 
+// The first pass's march length where none was chosen per problem: one pass covers all
+// problems, so their marches fill the chip together.
+static int common_rows(const gpm_batch *b)
+{
+    if (b->rows > 0) return b->rows;
+    return march_rows(b->prec, [&](int T) {
+        long long n = 0;
+        for (const gpm_ctx *c : b->ctx) n += first_pass_waves(c->nx, c->ny, T);
+        return n;
+    });
+}
+
 static void drop_graphs(gpm_batch *b)
 {
     for (int r = 0; r < 3; ++r)
@@ -142,9 +146,10 @@ static gpm_status build_tables(gpm_batch *b)
     std::vector<Cascade> casc(P);
     std::vector<int> blk(P + 1), dblk(P + 1);
     blk[0] = dblk[0] = 0;
+    const int rows = common_rows(b);
     for (int p = 0; p < P; ++p) {
         gpm_ctx *c = b->ctx[p];
-        c->rows = b->prow.empty() ? b->rows : b->prow[p];
+        c->rows = b->prow.empty() ? rows : b->prow[p];
         const Weights<real> &W = *(const Weights<real> *)(sizeof(real) == 8 ? (const void *)&c->w64 : (const void *)&c->w32);
         for (int r = 0; r < 3; ++r) {
             const int u0 = r, a = (r + 1) % 3, bb = (r + 2) % 3;
@@ -177,7 +182,7 @@ static gpm_status build_tables(gpm_batch *b)
         // tail_threshold troubled cells, then one workgroup per problem to the end
         C.tail_thr = c->tail_threshold;
         C.back_thr = 0x7fffffff;
-        blk[p + 1] = blk[p] + fp_blocks(c, c->rows);
+        blk[p + 1] = blk[p] + first_pass_waves(c->nx, c->ny, c->rows);
         dblk[p + 1] = dblk[p] + dt_blocks(c);
     }
     b->iso = 1;
@@ -480,7 +485,7 @@ gpm_status gpm_batch_autotune(gpm_batch *b, double cfl, int reps, int *rows_out,
                               : launch_batch_dt<float>(tabs<float>(b, b->cur, 0), b->ndt, b->casc, cfl, b->stream);
     BHIPCHK(b, de);
     std::vector<int> rows(P);
-    for (int p = 0; p < P; ++p) rows[p] = b->prow.empty() ? b->rows : b->prow[p];
+    for (int p = 0; p < P; ++p) rows[p] = b->prow.empty() ? common_rows(b) : b->prow[p];
     hipEvent_t e0, e1;
     BHIPCHK(b, hipEventCreate(&e0));
     BHIPCHK(b, hipEventCreate(&e1));

@@ -25,6 +25,36 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 }  // namespace
 
+// March length (rows per wavefront) of a first pass that takes waves(T) wavefronts in
+// marches of T rows.  A march of T rows runs T + 2 rows and a start-up worth half a row,
+// and the 1024 SIMDs hold two marches each in FP64, four in FP32; a row (radius 3,
+// measured) takes 8.3 us alone on its SIMD and 11.2 us beside another march in FP64, and
+// 5.8, 6.5, 8.1 and 9.7 us with one to four marches in FP32.  So a grid too small to fill
+// the chip takes short marches, one per SIMD at the least total (64^2 FP64: 12 rows 114
+// us, 1 row 24 us; 512^2: 12 rows 125 us, 3 rows 64 us), and a large one marches far
+// enough that the two extra rows cost little (2048^2 FP64: 4 rows 504 us, 10 rows 478
+// us).  Beyond 12 rows nothing is gained on any size (2048^2 at 24 rows: 502 us FP64,
+// 236 against 210 us FP32).
+template <typename Waves>
+static inline int march_rows(int prec, Waves waves)
+{
+    constexpr int kMax = 12;
+    constexpr long long kSimds = 1024;
+    static const double row_us[2][5] = {{0.0, 5.8, 6.5, 8.1, 9.7}, {0.0, 8.3, 11.2, 0.0, 0.0}};
+    const int d = prec == GPM_F64 ? 1 : 0, held = d ? 2 : 4;
+    int best = 1;
+    double tbest = 0.0;
+    for (int T = 1; T <= kMax; ++T) {
+        const long long w = (waves(T) + kSimds - 1) / kSimds;  // marches per SIMD
+        const double t = (T + 2.5) * ((double)(w / held) * row_us[d][held] + row_us[d][w % held]);
+        if (T == 1 || t < tbest) {
+            best = T;
+            tbest = t;
+        }
+    }
+    return best;
+}
+
 struct gpm_ctx {
     gpm_grid grid;
     int prec;
@@ -61,7 +91,7 @@ struct gpm_ctx {
     int passes_per_check = 4;  // smallest batch of multi-block cascade passes
     int head_guess = 4;        // batch length: the previous stage's multi-block passes + 2
     int tail_threshold = 32;   // troubled cells at or below which one workgroup finishes the cascade
-    int rows = 12;
+    int rows = 12;             // first-pass march length (march_rows, or gpm_set_tuning)
     int si0 = 0, si1 = 0;  // inflow slit cells [si0, si1)
     double slit_u[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};  // bottom, top
     double slit_lam = 0.0;  // the slit state's CFL bound (0: none)

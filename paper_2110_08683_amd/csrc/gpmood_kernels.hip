@@ -392,17 +392,16 @@ __device__ __forceinline__ void first_pass_wave(const StageArgs<real> &A, const 
 // faces begin; sums and node fluxes are formed where they stand (hold4); neighbours'
 // states come by lane shifts.  2048^2: 778 -> 502 us a launch in FP64, 301 -> 213 us in
 // FP32 (8-row marches), against 5778 -> 3463 and 3152 -> 2354 vector instructions.
-template <typename real, int RT, int WPB, bool ISO, bool HLL, bool BND>
-__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 4 : 2) void k_first_pass(const StageArgs<real>, const PassOut P)
+template <typename real, int RT, bool ISO, bool HLL, bool BND>
+__global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k_first_pass(const StageArgs<real>, const PassOut P)
 {
-    __shared__ real ring_all[WPB][8][4][LW];
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // the march's rows are scalar
+    __shared__ real ring[8][4][LW];
     // the first argument where it lies in the kernel's argument block: read through this
     // pointer a value is fetched again (a scalar load) rather than kept in a register
     // from the kernel's entry on
     const cptr<StageArgs<real>> A = (cptr<StageArgs<real>>)__builtin_amdgcn_kernarg_segment_ptr();
     first_pass_wave<real, RT, ISO, HLL, BND>(*(const StageArgs<real> *)A, P, &A->W,
-                                             xcd_tile(blockIdx.x, gridDim.x) * WPB + wv, ring_all[wv]);
+                                             xcd_tile(blockIdx.x, gridDim.x), ring);
 }
 
 // The claims of the cells the first pass lowered (listed in low, count *nlow):
@@ -1302,10 +1301,10 @@ __device__ __forceinline__ int find_problem(cptr<int> prefix, int n, int b)
     return lo;
 }
 
-template <typename real, int RT, int WPB, bool ISO, bool HLL, bool BND>
-__global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 4 : 2) void k_first_pass_batch(const BatchTabs<real> B)
+template <typename real, int RT, bool ISO, bool HLL, bool BND>
+__global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k_first_pass_batch(const BatchTabs<real> B)
 {
-    __shared__ real ring_all[WPB][8][4][LW];
+    __shared__ real ring[8][4][LW];
     cptr<int> blk = (cptr<int>)B.blk;
     const int p = find_problem(blk, B.nprob, blockIdx.x);
     const StageArgs<real> &A = table_entry(B.args, p);
@@ -1314,9 +1313,7 @@ __global__ __launch_bounds__(64 * WPB, sizeof(real) == 4 ? 4 : 2) void k_first_p
     // lowered cells are listed in clist[0]; k_claims_first_batch makes their claims
     Q.clist = C.clist[0];
     Q.ccount = &C.ctl->nlow;
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    first_pass_wave<real, RT, ISO, HLL, BND>(A, Q, &(((cptr<StageArgs<real>>)B.args) + p)->W,
-                                             (blockIdx.x - blk[p]) * WPB + wv, ring_all[wv]);
+    first_pass_wave<real, RT, ISO, HLL, BND>(A, Q, &(((cptr<StageArgs<real>>)B.args) + p)->W, blockIdx.x - blk[p], ring);
 }
 
 // Multi-block cascade passes of a batch.  Before each pass, k_batch_plan sizes
@@ -1550,30 +1547,29 @@ template <typename real, bool BW>
 static hipError_t launch_batch_stage_bw(const BatchTabs<real> &B, int top, int nfp_blocks, const Cascade *casc,
                                         hipStream_t st, bool tail = true)
 {
-    constexpr int WPB = sizeof(real) == 8 ? 2 : 4;
     const int nb = (B.nprob + 255) / 256;
     hipLaunchKernelGGL(k_reset_batch, dim3(nb), dim3(256), 0, st, casc, B.nprob);
-    const dim3 g(nfp_blocks), t(64 * WPB);
+    const dim3 g(nfp_blocks), t(64);
     if (B.solver == 1) {
         switch (top * 2 + (B.iso ? 1 : 0)) {
-        case 7: hipLaunchKernelGGL((k_first_pass_batch<real, 3, WPB, true, true, BW>), g, t, 0, st, B); break;
-        case 6: hipLaunchKernelGGL((k_first_pass_batch<real, 3, WPB, false, true, BW>), g, t, 0, st, B); break;
-        case 5: hipLaunchKernelGGL((k_first_pass_batch<real, 2, WPB, true, true, BW>), g, t, 0, st, B); break;
-        case 4: hipLaunchKernelGGL((k_first_pass_batch<real, 2, WPB, false, true, BW>), g, t, 0, st, B); break;
-        case 3: hipLaunchKernelGGL((k_first_pass_batch<real, 1, WPB, true, true, BW>), g, t, 0, st, B); break;
-        case 2: hipLaunchKernelGGL((k_first_pass_batch<real, 1, WPB, false, true, BW>), g, t, 0, st, B); break;
+        case 7: hipLaunchKernelGGL((k_first_pass_batch<real, 3, true, true, BW>), g, t, 0, st, B); break;
+        case 6: hipLaunchKernelGGL((k_first_pass_batch<real, 3, false, true, BW>), g, t, 0, st, B); break;
+        case 5: hipLaunchKernelGGL((k_first_pass_batch<real, 2, true, true, BW>), g, t, 0, st, B); break;
+        case 4: hipLaunchKernelGGL((k_first_pass_batch<real, 2, false, true, BW>), g, t, 0, st, B); break;
+        case 3: hipLaunchKernelGGL((k_first_pass_batch<real, 1, true, true, BW>), g, t, 0, st, B); break;
+        case 2: hipLaunchKernelGGL((k_first_pass_batch<real, 1, false, true, BW>), g, t, 0, st, B); break;
         default: return hipErrorInvalidValue;
         }
         if (!tail) return hipGetLastError();
         return B.walls ? launch_batch_cascade<real, true, true>(B, st) : launch_batch_cascade<real, false, true>(B, st);
     }
     switch (top * 2 + (B.iso ? 1 : 0)) {
-    case 7: hipLaunchKernelGGL((k_first_pass_batch<real, 3, WPB, true, false, BW>), g, t, 0, st, B); break;
-    case 6: hipLaunchKernelGGL((k_first_pass_batch<real, 3, WPB, false, false, BW>), g, t, 0, st, B); break;
-    case 5: hipLaunchKernelGGL((k_first_pass_batch<real, 2, WPB, true, false, BW>), g, t, 0, st, B); break;
-    case 4: hipLaunchKernelGGL((k_first_pass_batch<real, 2, WPB, false, false, BW>), g, t, 0, st, B); break;
-    case 3: hipLaunchKernelGGL((k_first_pass_batch<real, 1, WPB, true, false, BW>), g, t, 0, st, B); break;
-    case 2: hipLaunchKernelGGL((k_first_pass_batch<real, 1, WPB, false, false, BW>), g, t, 0, st, B); break;
+    case 7: hipLaunchKernelGGL((k_first_pass_batch<real, 3, true, false, BW>), g, t, 0, st, B); break;
+    case 6: hipLaunchKernelGGL((k_first_pass_batch<real, 3, false, false, BW>), g, t, 0, st, B); break;
+    case 5: hipLaunchKernelGGL((k_first_pass_batch<real, 2, true, false, BW>), g, t, 0, st, B); break;
+    case 4: hipLaunchKernelGGL((k_first_pass_batch<real, 2, false, false, BW>), g, t, 0, st, B); break;
+    case 3: hipLaunchKernelGGL((k_first_pass_batch<real, 1, true, false, BW>), g, t, 0, st, B); break;
+    case 2: hipLaunchKernelGGL((k_first_pass_batch<real, 1, false, false, BW>), g, t, 0, st, B); break;
     default: return hipErrorInvalidValue;
     }
     if (!tail) return hipGetLastError();
@@ -1622,21 +1618,17 @@ hipError_t launch_batch_stamp_restart(const Cascade *casc, int nprob, hipStream_
 template <typename real, int RT>
 static hipError_t launch_first_pass_rt(const StageArgs<real> &A, const PassOut &P, hipStream_t st)
 {
-    constexpr int WPB = sizeof(real) == 8 ? 2 : 4;
-    const int nstrip = (A.nx + 61) / 62, nseg = (A.ny + A.rows - 1) / A.rows;
-    const int nwave = nstrip * nseg;
-    const int nblk = (nwave + WPB - 1) / WPB;
-    const dim3 g(nblk), t(64 * WPB);
+    const dim3 g(first_pass_waves(A.nx, A.ny, A.rows)), t(64);
     const int bnd = (A.bcx == 2 || A.bcy == 2 || A.slit != 0) ? 4 : 0;
     switch (bnd + (A.solver == 1 ? 2 : 0) + (A.iso ? 1 : 0)) {
-    case 0: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, false, false, false>), g, t, 0, st, A, P); break;
-    case 1: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, true, false, false>), g, t, 0, st, A, P); break;
-    case 2: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, false, true, false>), g, t, 0, st, A, P); break;
-    case 3: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, true, true, false>), g, t, 0, st, A, P); break;
-    case 4: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, false, false, true>), g, t, 0, st, A, P); break;
-    case 5: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, true, false, true>), g, t, 0, st, A, P); break;
-    case 6: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, false, true, true>), g, t, 0, st, A, P); break;
-    default: hipLaunchKernelGGL((k_first_pass<real, RT, WPB, true, true, true>), g, t, 0, st, A, P); break;
+    case 0: hipLaunchKernelGGL((k_first_pass<real, RT, false, false, false>), g, t, 0, st, A, P); break;
+    case 1: hipLaunchKernelGGL((k_first_pass<real, RT, true, false, false>), g, t, 0, st, A, P); break;
+    case 2: hipLaunchKernelGGL((k_first_pass<real, RT, false, true, false>), g, t, 0, st, A, P); break;
+    case 3: hipLaunchKernelGGL((k_first_pass<real, RT, true, true, false>), g, t, 0, st, A, P); break;
+    case 4: hipLaunchKernelGGL((k_first_pass<real, RT, false, false, true>), g, t, 0, st, A, P); break;
+    case 5: hipLaunchKernelGGL((k_first_pass<real, RT, true, false, true>), g, t, 0, st, A, P); break;
+    case 6: hipLaunchKernelGGL((k_first_pass<real, RT, false, true, true>), g, t, 0, st, A, P); break;
+    default: hipLaunchKernelGGL((k_first_pass<real, RT, true, true, true>), g, t, 0, st, A, P); break;
     }
     return hipGetLastError();
 }

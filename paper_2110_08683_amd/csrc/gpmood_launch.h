@@ -8,6 +8,9 @@
 
 namespace gpm {
 
+// Wavefronts (one per block) of a first pass over an nx x ny grid in marches of `rows` rows.
+inline int first_pass_waves(int nx, int ny, int rows) { return ((nx + 61) / 62) * ((ny + rows - 1) / rows); }
+
 template <typename real>
 hipError_t launch_first_pass(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipEvent_t mid, hipStream_t st);
 template <typename real>
