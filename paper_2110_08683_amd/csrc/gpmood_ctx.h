@@ -233,6 +233,8 @@ static inline void fill_args(const gpm_ctx *c, const Weights<real> &W, StageArgs
     A.dx = (real)c->dx;
     A.dy = (real)c->dy;
     A.gamma = (real)c->grid.gamma;
+    A.inv_nx = 1.0 / c->nx;
+    A.inv_nx1 = 1.0 / (c->nx + 1);
     A.dx64 = c->dx;
     A.dy64 = c->dy;
     A.gamma64 = c->grid.gamma;

@@ -69,6 +69,7 @@ struct StageArgs {
     int next[4];          // next radius of the cascade after radius r
     real dx, dy, gamma, sigma_v, sigma_p, plat_thr, delta;
     double dx64, dy64, gamma64;  // the same in FP64 (the dt reduction)
+    double inv_nx, inv_nx1;      // 1 / nx, 1 / (nx + 1) (split_id)
     // general stage (s == 3): U_out = ca B + cb U*, U* = U_s - (dtf dt) F(U_s), B
     // passed as Un; dtf = 1 for the stages of eq. (rk3)
     double dtf;
@@ -148,31 +149,40 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
     return (b & 7) * per + (b >> 3);
 }
 
-// remap() for an index at most one period outside the axis (-n <= i < 2n): the
-// cascade reaches at most 4 cells beyond the domain, and periodic and reflecting
-// axes have at least 4 cells.  WALLS = false: the build for grids without a
-// reflecting axis (or for in-domain indices), which leaves out the mirror branch.
-template <bool WALLS = true>
+// remap() for an index at most one period outside a periodic or outflow axis (-n <= i <
+// 2n): the reconstructions reach at most 4 cells beyond the domain, and periodic axes
+// have at least 4 cells.
 __device__ __forceinline__ int wrap(int i, int n, int bc)
 {
     if (bc == 0) return i < 0 ? i + n : (i >= n ? i - n : i);
-    if (WALLS && bc == 2) return i < 0 ? -1 - i : (i >= n ? 2 * n - 1 - i : i);
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }
+
+// The same of many indices of one axis, reflecting walls included, without branches:
+// below the axis an index i maps to
+// m + lo, above it to m + hi, with m = (i & keep) ^ flip being i (periodic), 0 (outflow)
+// or -1 - i (reflecting).
+struct AxisMap {
+    int n, keep, flip, lo, hi;
+    __device__ __forceinline__ AxisMap(int n_, int bc)
+        : n(n_), keep(bc == 1 ? 0 : -1), flip(bc == 2 ? -1 : 0), lo(bc == 0 ? n_ : 0),
+          hi(bc == 0 ? -n_ : (bc == 1 ? n_ - 1 : 2 * n_))
+    {
+    }
+    __device__ __forceinline__ int operator()(int i) const
+    {
+        const int m = (i & keep) ^ flip, a = m + lo, b = m + hi;
+        const int r = i >= n ? b : i;
+        return i < 0 ? a : r;
+    }
+};
 
 // Is the gathered cell (i, j) (unwrapped indices) a ghost cell of the inflow slit?
 template <typename real>
 __device__ __forceinline__ bool in_slit(const StageArgs<real> &A, int i, int j)
 {
-    return i >= A.si0 && i < A.si1 && (((A.slit & 1) && j < 0) || ((A.slit & 2) && j >= A.ny));
-}
-
-// Factor of the momentum normal to an axis in the image of cell index i: -1 when
-// a reflecting wall (refl) mirrored the index, which reverses that momentum.
-template <typename real>
-__device__ __forceinline__ real msign(int i, int n, bool refl)
-{
-    return refl && (i < 0 || i >= n) ? real(-1) : real(1);
+    // plain logic on the conditions: no branches
+    return ((i >= A.si0) & (i < A.si1) & ((((A.slit & 1) != 0) & (j < 0)) | (((A.slit & 2) != 0) & (j >= A.ny)))) != 0;
 }
 
 // Division of the stage arithmetic: IEEE in FP64 (the parity path), in FP32 the
@@ -540,26 +550,66 @@ __device__ __forceinline__ int lane_here()
     return l;
 }
 
-// The value of the next (OFF = +1) or previous (OFF = -1) lane of the wavefront, by a
-// data-parallel shift: one vector move per 32 bits, with no LDS round trip.  Lane 63
-// (lane 0) gets zero.
-template <int OFF>
-__device__ __forceinline__ int lane_shift(int x)
+// Data-parallel move between lanes (CTRL: the instruction's lane pattern), one vector
+// move per 32 bits with no LDS round trip; a lane without a source gets zero.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x)
 {
-    static_assert(OFF == 1 || OFF == -1, "one lane");
-    return __builtin_amdgcn_update_dpp(0, x, OFF == 1 ? 0x130 : 0x138, 0xf, 0xf, true);  // wave_shl:1, wave_shr:1
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
 }
-template <int OFF>
-__device__ __forceinline__ float lane_shift(float x)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x)
 {
-    return __builtin_bit_cast(float, lane_shift<OFF>(__builtin_bit_cast(int, x)));
+    return __builtin_bit_cast(float, dpp<CTRL>(__builtin_bit_cast(int, x)));
 }
-template <int OFF>
-__device__ __forceinline__ double lane_shift(double x)
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x)
 {
     const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = (unsigned)lane_shift<OFF>((int)(unsigned)b), hi = (unsigned)lane_shift<OFF>((int)(unsigned)(b >> 32));
+    const unsigned lo = (unsigned)dpp<CTRL>((int)(unsigned)b), hi = (unsigned)dpp<CTRL>((int)(unsigned)(b >> 32));
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// The value of the next (OFF = +1) or previous (OFF = -1) lane of the wavefront; lane 63
+// (lane 0) gets zero.
+template <int OFF, typename T>
+__device__ __forceinline__ T lane_shift(T x)
+{
+    static_assert(OFF == 1 || OFF == -1, "one lane");
+    return dpp<OFF == 1 ? 0x130 : 0x138>(x);  // wave_shl:1, wave_shr:1
+}
+
+// The value of lane K of this lane's quad (all four lanes must be active).
+template <int K, typename T>
+__device__ __forceinline__ T quad(T x)
+{
+    return dpp<K * 0x55>(x);  // quad_perm:[K,K,K,K]
+}
+
+// Set bits of a wavefront's lane mask below this lane.
+__device__ __forceinline__ int below(unsigned long long mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// Element k of a short array by selects (an indexed read of a kernel argument would put
+// the arguments in memory).
+template <typename real>
+__device__ __forceinline__ real pick4(int k, const real (&x)[4])
+{
+    return k == 0 ? x[0] : (k == 1 ? x[1] : (k == 2 ? x[2] : x[3]));
+}
+
+// id = i + j * n for 0 <= id < 2^31 (inv = 1.0 / n, rounded): the quotient of the FP64
+// product is j or, where id is a multiple of n and the product fell short, j - 1.
+__device__ __forceinline__ void split_id(int id, int n, double inv, int &i, int &j)
+{
+    j = (int)((double)id * inv);
+    i = id - j * n;
+    if (i >= n) {
+        i -= n;
+        ++j;
+    }
 }
 
 // A value the whole wavefront holds, made scalar.
@@ -661,24 +711,6 @@ __device__ __forceinline__ void wave_count(bool flag, int *count)
 {
     const unsigned long long mask = __ballot(flag);
     if (mask != 0ull && (threadIdx.x & 63) == 0) atomicAdd(count, (int)__popcll(mask));
-}
-
-// Reserve n slots per lane (n < 1024) in one list with one atomic per wavefront;
-// returns the lane's first slot.  Must be reached by all 64 lanes together.
-__device__ __forceinline__ int wave_reserve(int n, int *count)
-{
-    const int lane = threadIdx.x & 63;
-    int incl = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-    }
-    const int tot = __shfl(incl, 63);
-    int b = 0;
-    if (lane == 63 && tot != 0) b = atomicAdd(count, tot);
-    b = __shfl(b, 63);
-    return b + incl - n;
 }
 
 // Reserve n slots per lane in two lists at once (n = count0 + 65536 * count1,

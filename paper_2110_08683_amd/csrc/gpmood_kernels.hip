@@ -29,83 +29,16 @@
 
 namespace gpm {
 
+// The kernel's first argument where it lies in the kernel's argument block: read through
+// this reference a value is fetched again (a scalar load) rather than kept in a register
+// from the kernel's entry on.
+template <typename T>
+__device__ __forceinline__ const T &first_arg()
+{
+    return *(const T *)(cptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 constexpr int LW = 70;  // LDS columns per ring row: 64 lanes + 3 halo columns each side
-
-// Claims after lowering cell (i, j) (act = this lane lowered it): its four faces
-// (and, on periodic axes, the duplicate copy of a boundary face) are listed for
-// recomputation in the next pass, and the cell with its four face neighbours for
-// re-evaluation.  A stamp per face and per cell keeps each list duplicate-free.
-// Must be reached by all 64 lanes of the wavefront together.
-template <typename real>
-__device__ __forceinline__ void claim_ids(const StageArgs<real> &A, int i, int j, int (&fid)[6], bool (&fok)[6],
-                                          int (&cid)[5], bool (&cok)[5])
-{
-    const int nx = A.nx, ny = A.ny;
-    const int nfx = (nx + 1) * ny;
-    // faces: x faces i, i+1 of row j; y faces j, j+1 of column i; periodic duplicates
-    fid[0] = j * (nx + 1) + i;
-    fid[1] = j * (nx + 1) + i + 1;
-    fid[2] = nfx + j * nx + i;
-    fid[3] = nfx + (j + 1) * nx + i;
-    fok[0] = fok[1] = fok[2] = fok[3] = true;
-    fok[4] = A.bcx == 0 && (i == 0 || i == nx - 1);
-    fid[4] = fok[4] ? (i == 0 ? j * (nx + 1) + nx : j * (nx + 1)) : fid[0];  // copy of face 0 / face nx
-    fok[5] = A.bcy == 0 && (j == 0 || j == ny - 1);
-    fid[5] = fok[5] ? (j == 0 ? nfx + ny * nx + i : nfx + i) : fid[2];      // copy of face 0 / face ny
-    const int di[5] = {0, -1, 1, 0, 0}, dj[5] = {0, 0, 0, -1, 1};
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int ii = i + di[k], jj = j + dj[k];
-        cok[k] = (A.bcx == 0 || (ii >= 0 && ii < nx)) && (A.bcy == 0 || (jj >= 0 && jj < ny));
-        // (on a non-periodic axis only in-domain indices get here: no mirror needed)
-        cid[k] = cok[k] ? wrap<false>(jj, ny, A.bcy) * nx + wrap<false>(ii, nx, A.bcx) : j * nx + i;
-    }
-}
-
-template <typename real>
-__device__ __forceinline__ void claim_after_lowering(const StageArgs<real> &A, const PassOut &P, int i, int j,
-                                                     bool act)
-{
-    int fid[6], cid[5];
-    bool fok[6], cok[5];
-    claim_ids(A, i, j, fid, fok, cid, cok);
-    bool fmine[6], cmine[5];
-    int nmine = 0;
-    if (act) {
-        // all eleven stamp updates are issued back to back; an entry that does not
-        // apply updates its own cell or face with 0, which changes nothing
-        unsigned fo[6], co[5];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) fo[k] = atomicMax(&A.fstamp[fid[k]], fok[k] ? P.stamp : 0u);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) co[k] = atomicMax(&A.cstamp[cid[k]], cok[k] ? P.stamp : 0u);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            fmine[k] = fok[k] && fo[k] < P.stamp;
-            nmine += fmine[k] ? 1 : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            cmine[k] = cok[k] && co[k] < P.stamp;
-            nmine += cmine[k] ? 65536 : 0;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) fmine[k] = false;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) cmine[k] = false;
-    }
-    int fb, cb;
-    wave_reserve2(nmine, P.fcount, P.ccount, fb, cb);
-    if (nmine != 0) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            if (fmine[k]) P.flist[fb++] = fid[k];
-#pragma unroll
-        for (int k = 0; k < 5; ++k)
-            if (cmine[k]) P.clist[cb++] = cid[k];
-    }
-}
 
 // One wavefront's strip (tile wid of the problem) of the first pass; ring is the
 // wavefront's LDS ring.  ISO: A.iso is 1 (the y states read the x weights).
@@ -396,36 +329,8 @@ template <typename real, int RT, bool ISO, bool HLL, bool BND>
 __global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k_first_pass(const StageArgs<real>, const PassOut P)
 {
     __shared__ real ring[8][4][LW];
-    // the first argument where it lies in the kernel's argument block: read through this
-    // pointer a value is fetched again (a scalar load) rather than kept in a register
-    // from the kernel's entry on
-    const cptr<StageArgs<real>> A = (cptr<StageArgs<real>>)__builtin_amdgcn_kernarg_segment_ptr();
-    first_pass_wave<real, RT, ISO, HLL, BND>(*(const StageArgs<real> *)A, P, &A->W,
-                                             xcd_tile(blockIdx.x, gridDim.x), ring);
-}
-
-// The claims of the cells the first pass lowered (listed in low, count *nlow):
-// the same claims, stamps and lists as if they had been made in the pass.
-template <typename real>
-__global__ __launch_bounds__(256) void k_claims_first(const StageArgs<real> A, const PassOut P, const int *low,
-                                                      const int *nlow)
-{
-    const int n = *nlow;
-    PassOut Q = P;
-    Q.stamp = *A.stamp0;
-    const int stride = gridDim.x * blockDim.x;
-    const int nround = (n + stride - 1) / stride;
-    for (int r = 0; r < nround; ++r) {
-        const int t = r * stride + blockIdx.x * blockDim.x + threadIdx.x;
-        const bool act = t < n;
-        int i = 0, j = 0;
-        if (act) {
-            const int c = low[t];
-            j = c / A.nx;
-            i = c - j * A.nx;
-        }
-        claim_after_lowering(A, Q, i, j, act);
-    }
+    const StageArgs<real> &A = first_arg<StageArgs<real>>();
+    first_pass_wave<real, RT, ISO, HLL, BND>(A, P, &((cptr<StageArgs<real>>)&A)->W, xcd_tile(blockIdx.x, gridDim.x), ring);
 }
 
 // ------------------------------------------------------------- cascade pass
@@ -445,13 +350,12 @@ __device__ __forceinline__ void hllc_rt(real g, int dir, const real (&UL)[4], co
     F[3] = f[3];
 }
 
-// Per-wavefront LDS of the cascade's face work: 16 faces x 4 lanes, each lane with
-// the 4 left and 4 right node states of its variable (later: one node's flux),
-// and one flag word per lane.
+// Per-wavefront LDS of the cascade's face work: eight faces of eight lanes, each lane's
+// states of its variable and side at up to three nodes, and the nodes' fluxes.
 template <typename real>
 struct FaceXchg {
-    real s[64][8];
-    int fl[64];
+    real s[64][3];
+    real f[8][3][4];
 };
 
 // Copy the compact weight table into LDS (all NT threads of the block, every
@@ -474,247 +378,208 @@ __device__ __forceinline__ void load_gtab(const real *gtab, real *wl)
     }
 }
 
+// The radius-2 diamond, ring by ring.
+constexpr int kD13[13][2] = {{0, 0},  {-1, 0}, {1, 0},   {0, -1}, {0, 1},  {-2, 0}, {2, 0},
+                             {0, -2}, {0, 2},  {-1, -1}, {1, -1}, {-1, 1}, {1, 1}};
+
+// Columns and row offsets of the cells up to two away from cell (i, j) (unwrapped, at most
+// one cell outside the grid), boundary conditions applied.  Returns whether some lane of
+// the wavefront (all active) has one of them outside the grid.
+template <typename real>
+__device__ __forceinline__ bool near_cells(const StageArgs<real> &A, int i, int j, int (&xc)[5], int (&yr)[5])
+{
+    const int nx = A.nx, ny = A.ny;
+    const bool out = __any(((i < 2) | (i >= nx - 2) | (j < 2) | (j >= ny - 2)) != 0) != 0;
+    if (!out) {
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            xc[d] = i + d - 2;
+            yr[d] = j * nx + (d - 2) * nx;
+        }
+    } else {
+        const AxisMap X(nx, A.bcx), Y(ny, A.bcy);
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            xc[d] = X(i + d - 2);
+            yr[d] = Y(j + d - 2) * nx;
+        }
+    }
+    return out;
+}
+
 // Cascade pass, part 1: recompute the listed faces at their EDP_1 order (the
-// smaller radius of the two cells), four lanes per face.  Lane v of a quad
-// gathers variable v of both cells' quarter positions (all loads issued at once),
-// forms that variable's states at every Gauss node, and after an LDS transpose
-// lane k solves the HLLC problem of node k; lane v then sums variable v of the
-// node fluxes with the Gauss weights (eq. (fvm_F)).  The products and sums are
-// those of the first pass (build_Q, states_dir, hllc), in the same order, with
-// the multiplicity of on-axis positions folded into the table weights.
+// smaller radius of the two cells), eight lanes per face: lane 4 side + v gathers
+// variable v around the cell on its side and forms that variable's states at every
+// Gauss node; after an LDS transpose lane k solves the Riemann problem of node k, and
+// lane v sums variable v of the node fluxes with the Gauss weights (eq. (fvm_F)).  The
+// sums and products are those of the first pass, in the same order, with the
+// multiplicity of on-axis positions folded into the table weights.
 //
-// A listed face borders a cell lowered in the previous evaluation, so its radius
-// is below the top radius: at most 2 for GP-MOOD7.  Radius 3 (positions 6..9) is
-// still handled, by a rolled loop.  The number of rounds is uniform across the
-// wavefront (LDS exchange); wl is the LDS copy of the compact weight table.
-// pre: when use_pre, this thread's list entry of round 0, loaded by the caller
-// (while the count was still unknown).
+// A pass has few faces and waits for each step of this chain in turn, so what counts is
+// the length of one lane's instruction stream.  Eight lanes of one side each, the 13
+// cells of the diamond loaded once (its positions' mirror images coincide on the axes),
+// a transposed face's axes exchanged in the addresses, boundary indices without
+// branches and products with the table's zeros left out make it 567 vector instructions
+// in FP64 against 1542 with four lanes of both sides and 48 loads each.  With the cells'
+// part below, a 160-step run at 512^2 in FP64 went from 306 to 211 ms, a step of the
+// 400^2 box with walls from 1.97 to 0.72 ms.
+//
+// A listed face borders a cell lowered in an earlier evaluation of this stage, so its
+// radius is below the top radius: at most 2.  Every lane of the wavefront runs with a
+// valid face (lanes past the list repeat an entry and store nothing); wl is the LDS copy
+// of the compact weight table.  slot: this lane's place among the per faces of a round.
+// pre: when use_pre, its list entry of the first round, loaded by the caller (while the
+// count was still unknown; any face id).
 template <bool WALLS, bool HLL, typename real>
 __device__ __forceinline__ void faces_phase(const StageArgs<real> &A, const real *wl, FaceXchg<real> &X,
-                                            const int *flist, int n, int t0, int stride, int pre = 0,
+                                            const int *flist, int n, int slot, int per, int pre = 0,
                                             bool use_pre = false)
 {
     const int nx = A.nx, ny = A.ny;
     const int nfx = (nx + 1) * ny, nfy = nx * (ny + 1);
     const size_t plane = (size_t)nx * ny;
-    const int lane = threadIdx.x & 63, v = lane & 3, q0 = lane & ~3;
-    const int nround = (4 * n + stride - 1) / stride;
-    for (int r = 0; r < nround; ++r) {
-        const int idx = (r * stride + t0) >> 2;
+    const int lane = threadIdx.x & 63, l8 = lane & 7, oct = lane >> 3, v = lane & 3, side = (lane >> 2) & 1;
+    for (int base = 0; base < n; base += per) {
+        const int idx = base + slot;
+        if (__builtin_amdgcn_readfirstlane(idx) >= n) break;  // nothing (more) for this wavefront
         const bool valid = idx < n;
-        int dir = 0, R = 0, fo = 0;
-        bool tr = false;
-        real PL[2][4], PR[2][4];  // [slot][component] of variable v, left and right cell
+        const int f = (use_pre && base == 0) ? pre : flist[valid ? idx : n - 1];
+        const int dir = f >= nfx ? 1 : 0, fo = dir ? f - nfx : f;
+        int i, j;
+        split_id(fo, dir ? nx : nx + 1, dir ? A.inv_nx : A.inv_nx1, i, j);
+        // this lane's cell: (i, j) on the + side of the face, one step back on the - side
+        const int ic = i - (side == 0 && dir == 0 ? 1 : 0), jc = j - (side == 0 && dir == 1 ? 1 : 0);
+        int xc[5], yr[5];
+        const bool out = near_cells(A, ic, jc, xc, yr);
+        const int o = A.order[yr[2] + xc[2]];  // issued ahead of the stencil loads
+        // an isotropic y face computes what an x face computes on the transposed
+        // grid: position (a, b) is gathered at offset (b, a) and the x table used
+        const bool tr = dir == 1 && A.iso;
+        const real *U = A.Us + v * plane;
+        real q[13];
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
+        for (int m = 0; m < 13; ++m) {
+            const int a = kD13[m][0] + 2, b = kD13[m][1] + 2;
+            q[m] = U[(unsigned)((tr ? yr[a] : xc[a]) + (tr ? xc[b] : yr[b]))];
+        }
+        if (WALLS) {
+            // reflecting walls reverse the normal momentum of mirrored cells; an inflow
+            // slit's ghost cells hold the injected state
+            // (plain logic on the conditions: no branch per cell)
+            if (out) {
+                const int fx = (v == 1) & (A.bcx == 2), fy = (v == 2) & (A.bcy == 2);
+                real sb[4], st[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) PL[p][c] = PR[p][c] = real(0);
-        if (valid) {
-            const int f = (use_pre && r == 0) ? pre : flist[idx];
-            int iL, jL, cL, cR;
-            if (f < nfx) {
-                const int j = f / (nx + 1), i = f - j * (nx + 1);  // between cells i-1 and i
-                dir = 0;
-                fo = f;
-                iL = i - 1;
-                jL = j;
-                cL = j * nx + wrap<WALLS>(i - 1, nx, A.bcx);
-                cR = j * nx + wrap<WALLS>(i, nx, A.bcx);
-            } else {
-                const int g = f - nfx;
-                const int j = g / nx, i = g - j * nx;  // between cells (i, j-1) and (i, j)
-                dir = 1;
-                fo = g;
-                iL = i;
-                jL = j - 1;
-                cL = wrap<WALLS>(j - 1, ny, A.bcy) * nx + i;
-                cR = wrap<WALLS>(j, ny, A.bcy) * nx + i;
-            }
-            const int iR = iL + (dir == 0), jR = jL + (dir == 1);
-            const int oL = A.order[cL], oR = A.order[cR];  // issued ahead of the stencil loads
-            // an isotropic y face computes what an x face computes on the transposed
-            // grid: position (a, b) is gathered at offset (b, a) and the x table used
-            tr = dir == 1 && A.iso;
-            const real *U = A.Us + v * plane;
-            // a gathered cell (xr, yr) (unwrapped) at wrapped offset yo + xo, sign sg;
-            // the walls build also puts an inflow slit's state in its ghost cells
-            const real slitb = A.slitU[0][v], slitt = A.slitU[1][v];
-            auto gv = [&](int xr, int yr, size_t yo, int xo, real sg) -> real {
-                return (WALLS && A.slit && in_slit(A, xr, yr)) ? (yr < 0 ? slitb : slitt) : sg * U[yo + xo];
-            };
-            // reflecting walls reverse the normal momentum of mirrored cells (WALLS:
-            // the variant built for grids with a reflecting axis)
-            const bool fx = WALLS && v == 1 && A.bcx == 2, fy = WALLS && v == 2 && A.bcy == 2;
-            // quarter positions 0..5 (radius <= 2) of both cells: 48 independent loads
-            constexpr int pa[6] = {0, 1, 0, 2, 0, 1}, pb[6] = {0, 0, 1, 0, 2, 1};
-            real QL[6][4], QR[6][4];
-#pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                const int xLp = wrap<WALLS>(iL + pa[e], nx, A.bcx), xLm = wrap<WALLS>(iL - pa[e], nx, A.bcx);
-                const int xRp = wrap<WALLS>(iR + pa[e], nx, A.bcx), xRm = wrap<WALLS>(iR - pa[e], nx, A.bcx);
-                const size_t yLp = (size_t)wrap<WALLS>(jL + pb[e], ny, A.bcy) * nx;
-                const size_t yLm = (size_t)wrap<WALLS>(jL - pb[e], ny, A.bcy) * nx;
-                const size_t yRp = (size_t)wrap<WALLS>(jR + pb[e], ny, A.bcy) * nx;
-                const size_t yRm = (size_t)wrap<WALLS>(jR - pb[e], ny, A.bcy) * nx;
-                const real sLp = msign<real>(iL + pa[e], nx, fx), sLm = msign<real>(iL - pa[e], nx, fx);
-                const real sRp = msign<real>(iR + pa[e], nx, fx), sRm = msign<real>(iR - pa[e], nx, fx);
-                const real tLp = msign<real>(jL + pb[e], ny, fy), tLm = msign<real>(jL - pb[e], ny, fy);
-                const real tRp = msign<real>(jR + pb[e], ny, fy), tRm = msign<real>(jR - pb[e], ny, fy);
-                const int a = pa[e], b = pb[e];
-                parity4(gv(iL + a, jL + b, yLp, xLp, sLp * tLp), gv(iL - a, jL + b, yLp, xLm, sLm * tLp),
-                        gv(iL + a, jL - b, yLm, xLp, sLp * tLm), gv(iL - a, jL - b, yLm, xLm, sLm * tLm), QL[e]);
-                parity4(gv(iR + a, jR + b, yRp, xRp, sRp * tRp), gv(iR - a, jR + b, yRp, xRm, sRm * tRp),
-                        gv(iR + a, jR - b, yRm, xRp, sRp * tRm), gv(iR - a, jR - b, yRm, xRm, sRm * tRm), QR[e]);
-            }
-            // a transposed y face takes position (a, b) from the gathered (b, a), OE and
-            // EO exchanged: with the diagonal pairing these are the bits a transposed
-            // gather would give
-            constexpr int T6[6] = {0, 2, 1, 4, 3, 5};
-#pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                if (T6[e] == e) {
-                    const real lo = QL[e][C_OE], ro = QR[e][C_OE];
-                    QL[e][C_OE] = tr ? QL[e][C_EO] : lo;
-                    QL[e][C_EO] = tr ? lo : QL[e][C_EO];
-                    QR[e][C_OE] = tr ? QR[e][C_EO] : ro;
-                    QR[e][C_EO] = tr ? ro : QR[e][C_EO];
-                } else if (T6[e] > e) {
-                    const int f = T6[e];
-                    real l0[4], l1[4], r0[4], r1[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        l0[c] = QL[e][c]; l1[c] = QL[f][c];
-                        r0[c] = QR[e][c]; r1[c] = QR[f][c];
-                    }
-                    QL[e][C_EE] = tr ? l1[C_EE] : l0[C_EE];
-                    QL[e][C_OO] = tr ? l1[C_OO] : l0[C_OO];
-                    QL[e][C_OE] = tr ? l1[C_EO] : l0[C_OE];
-                    QL[e][C_EO] = tr ? l1[C_OE] : l0[C_EO];
-                    QL[f][C_EE] = tr ? l0[C_EE] : l1[C_EE];
-                    QL[f][C_OO] = tr ? l0[C_OO] : l1[C_OO];
-                    QL[f][C_OE] = tr ? l0[C_EO] : l1[C_OE];
-                    QL[f][C_EO] = tr ? l0[C_OE] : l1[C_EO];
-                    QR[e][C_EE] = tr ? r1[C_EE] : r0[C_EE];
-                    QR[e][C_OO] = tr ? r1[C_OO] : r0[C_OO];
-                    QR[e][C_OE] = tr ? r1[C_EO] : r0[C_OE];
-                    QR[e][C_EO] = tr ? r1[C_OE] : r0[C_EO];
-                    QR[f][C_EE] = tr ? r0[C_EE] : r1[C_EE];
-                    QR[f][C_OO] = tr ? r0[C_OO] : r1[C_OO];
-                    QR[f][C_OE] = tr ? r0[C_EO] : r1[C_OE];
-                    QR[f][C_EO] = tr ? r0[C_OE] : r1[C_EO];
+                for (int u = 0; u < 4; ++u) {
+                    sb[u] = A.slitU[0][u];
+                    st[u] = A.slitU[1][u];
                 }
-            }
-            R = min(oL, oR);
-            const real *wt = wl + (R * 2 + (tr ? 0 : dir)) * kGtabPerDir;
-            const int np = R <= 0 ? 1 : (R == 1 ? 3 : (R == 2 ? 6 : 10));
+                hold4(sb);
+                hold4(st);
+                const real svb = pick4(v, sb), svt = pick4(v, st);
 #pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                if (e < np) {
-#pragma unroll
-                    for (int p = 0; p < 2; ++p)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            const real w = wt[p * (kNPos * 4) + e * 4 + c];
-                            PL[p][c] = fma(w, QL[e][c], PL[p][c]);
-                            PR[p][c] = fma(w, QR[e][c], PR[p][c]);
-                        }
+                for (int m = 0; m < 13; ++m) {
+                    const int x = ic + (tr ? kD13[m][1] : kD13[m][0]), y = jc + (tr ? kD13[m][0] : kD13[m][1]);
+                    const int neg = (fx & ((unsigned)x >= (unsigned)nx)) | (fy & ((unsigned)y >= (unsigned)ny));
+                    q[m] *= neg ? real(-1) : real(1);
+                    q[m] = in_slit(A, x, y) ? (y < 0 ? svb : svt) : q[m];
                 }
-            }
-#pragma unroll 1
-            for (int e = 6; e < np; ++e) {
-                const int a0 = (int)((kPosA >> (4 * e)) & 15u), b0 = (int)((kPosB >> (4 * e)) & 15u);
-                const int a = tr ? b0 : a0, b = tr ? a0 : b0;  // x and y offsets
-                const int xLp = wrap<WALLS>(iL + a, nx, A.bcx), xLm = wrap<WALLS>(iL - a, nx, A.bcx);
-                const int xRp = wrap<WALLS>(iR + a, nx, A.bcx), xRm = wrap<WALLS>(iR - a, nx, A.bcx);
-                const size_t yLp = (size_t)wrap<WALLS>(jL + b, ny, A.bcy) * nx, yLm = (size_t)wrap<WALLS>(jL - b, ny, A.bcy) * nx;
-                const size_t yRp = (size_t)wrap<WALLS>(jR + b, ny, A.bcy) * nx, yRm = (size_t)wrap<WALLS>(jR - b, ny, A.bcy) * nx;
-                const real sLp = msign<real>(iL + a, nx, fx), sLm = msign<real>(iL - a, nx, fx);
-                const real sRp = msign<real>(iR + a, nx, fx), sRm = msign<real>(iR - a, nx, fx);
-                const real tLp = msign<real>(jL + b, ny, fy), tLm = msign<real>(jL - b, ny, fy);
-                const real tRp = msign<real>(jR + b, ny, fy), tRm = msign<real>(jR - b, ny, fy);
-                const real Lpp = gv(iL + a, jL + b, yLp, xLp, sLp * tLp), Lmm = gv(iL - a, jL - b, yLm, xLm, sLm * tLm);
-                const real Lx = gv(iL - a, jL + b, yLp, xLm, sLm * tLp), Ly = gv(iL + a, jL - b, yLm, xLp, sLp * tLm);
-                const real Lpm = tr ? Lx : Ly, Lmp = tr ? Ly : Lx;
-                const real Rpp = gv(iR + a, jR + b, yRp, xRp, sRp * tRp), Rmm = gv(iR - a, jR - b, yRm, xRm, sRm * tRm);
-                const real Rx = gv(iR - a, jR + b, yRp, xRm, sRm * tRp), Ry = gv(iR + a, jR - b, yRm, xRp, sRp * tRm);
-                const real Rpm = tr ? Rx : Ry, Rmp = tr ? Ry : Rx;
-                real ql[4], qr[4];
-                parity4(Lpp, Lmp, Lpm, Lmm, ql);
-                parity4(Rpp, Rmp, Rpm, Rmm, qr);
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const real w = wt[p * (kNPos * 4) + e * 4 + c];
-                        PL[p][c] = fma(w, ql[c], PL[p][c]);
-                        PR[p][c] = fma(w, qr[c], PR[p][c]);
-                    }
             }
         }
-        const int q = R <= 0 ? 1 : R + 1;
-        // states of variable v at node k (table order; slot 1 is the inner pair for
-        // R = 3 and the centre node for R = 2; a single node has no +- partner)
+        // row_half_mirror: a lane of the other side.  A listed face's radius is at most 2; a
+        // lane past the list may hold any face, which is taken at radius 2 as well (its
+        // nodes must stay within its own slots of X).
+        const int R = min(min(o, dpp<0x141>(o)), 2);
+        const real *wt = wl + (R * 2 + (tr ? 0 : dir)) * kGtabPerDir;
+        auto w = [&](int p, int e, int c) { return wt[p * (kNPos * 4) + e * 4 + c]; };
+        // The parity sums of kQ's positions, the mirror cells of an axis position taken
+        // once and doubled (twice at the centre), which is exact.  z: the vanishing sums
+        // of the centre (zero, or not a number where the cell is not finite).
+        real P[2][4];
+        {
+            const real ee = (q[0] + q[0]) + (q[0] + q[0]), z = q[0] - q[0];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int slot = (R >= 2 && k >= 1 && k <= q - 2) ? 1 : 0;
-            const bool single = R <= 0 || (R == 2 && k == 1);
-            const bool plus = k < (q >> 1);
-            const real lee = slot ? PL[1][C_EE] : PL[0][C_EE], loe = slot ? PL[1][C_OE] : PL[0][C_OE];
-            const real leo = slot ? PL[1][C_EO] : PL[0][C_EO], loo = slot ? PL[1][C_OO] : PL[0][C_OO];
-            const real ree = slot ? PR[1][C_EE] : PR[0][C_EE], roe = slot ? PR[1][C_OE] : PR[0][C_OE];
-            const real reo = slot ? PR[1][C_EO] : PR[0][C_EO], roo = slot ? PR[1][C_OO] : PR[0][C_OO];
+            for (int p = 0; p < 2; ++p) {
+                P[p][C_EE] = fma(w(p, 0, C_EE), ee, real(0));
+                P[p][C_OE] = P[p][C_EO] = P[p][C_OO] = z;
+            }
+        }
+        auto axis = [&](int e, real plus, real minus, int odd) {
+            const real s = plus + minus, d = plus - minus, ee = s + s, od = d + d;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                P[p][C_EE] = fma(w(p, e, C_EE), ee, P[p][C_EE]);
+                P[p][odd] = fma(w(p, e, odd), od, P[p][odd]);
+            }
+        };
+        if (R >= 1) {
+            axis(1, q[2], q[1], C_OE);
+            axis(2, q[4], q[3], C_EO);
+        }
+        if (R >= 2) {
+            axis(3, q[6], q[5], C_OE);
+            axis(4, q[8], q[7], C_EO);
+            real d[4];
+            parity4(q[12], q[11], q[10], q[9], d);  // (+, +), (-, +), (+, -), (-, -)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) P[p][c] = fma(w(p, 5, c), d[c], P[p][c]);
+        }
+        // states at the nodes (table order; slot 1 is the centre node of R = 2, a single
+        // node has no +- partner): the + face of the lower cell, the - face of the upper
+        {
             // odd across / along the face (a transposed y face is in the x-face frame)
             const bool yframe = dir == 1 && !tr;
-            const real lF = yframe ? leo : loe, lN = yframe ? loe : leo;
-            const real rF = yframe ? reo : roe, rN = yframe ? roe : reo;
-            const real Ap = lee + lF, Cp = lN + loo;  // + face of the left cell
-            const real Bm = ree - rF, Dm = rN - roo;  // - face of the right cell
-            X.s[lane][k] = single ? Ap : (plus ? Ap + Cp : Ap - Cp);
-            X.s[lane][4 + k] = single ? Bm : (plus ? Bm + Dm : Bm - Dm);
+            const real F0 = yframe ? P[0][C_EO] : P[0][C_OE], N0 = yframe ? P[0][C_OE] : P[0][C_EO];
+            const real F1 = yframe ? P[1][C_EO] : P[1][C_OE];
+            const real A0 = side ? P[0][C_EE] - F0 : P[0][C_EE] + F0, A1 = side ? P[1][C_EE] - F1 : P[1][C_EE] + F1;
+            const real C0 = side ? N0 - P[0][C_OO] : N0 + P[0][C_OO];
+            const real sp = A0 + C0, sm = A0 - C0;
+            X.s[lane][0] = R <= 0 ? A0 : sp;
+            X.s[lane][1] = R == 2 ? A1 : sm;
+            X.s[lane][2] = sm;
         }
         wave_lds_sync();
-        real fk[4] = {real(0), real(0), real(0), real(0)};
-        int flg = 0;
-        if (valid && v < q) {  // lane v solves node k = v
+        const int nq = R <= 0 ? 1 : R + 1, k = min(l8, nq - 1);
+        real fk[4];
+        bool bl, br;
+        {
             real UL[4], UR[4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                UL[w] = X.s[q0 + w][v];
-                UR[w] = X.s[q0 + w][4 + v];
+            for (int u = 0; u < 4; ++u) {
+                UL[u] = X.s[oct * 8 + u][k];
+                UR[u] = X.s[oct * 8 + 4 + u][k];
             }
-            bool bl, br;
             hllc_rt<HLL>(A.gamma, dir, UL, UR, fk, bl, br);
-            flg = (bl ? 1 : 0) | (br ? 2 : 0);
+        }
+        // the lanes past the last node repeat it: no need to leave them out
+        const unsigned ml = (unsigned)(__ballot(bl) >> (oct * 8)) & 0xffu, mr = (unsigned)(__ballot(br) >> (oct * 8)) & 0xffu;
+        if (l8 < nq) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) X.f[oct][l8][u] = fk[u];
         }
         wave_lds_sync();
-#pragma unroll
-        for (int w = 0; w < 4; ++w) X.s[lane][w] = fk[w];
-        X.fl[lane] = flg;
-        wave_lds_sync();
-        if (valid) {
-            real F = real(0);
-            int fl = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (k < q) {
-                    const int slot = (R >= 2 && k >= 1 && k <= q - 2) ? 1 : 0;
-                    if constexpr (HLL) {
-                        // mirror-paired quadrature (see the first pass's y faces)
-                        if (2 * k + 1 == q) F = fma(wl[kGtabNodeOff + R * 2 + slot], X.s[q0 + k][v], F);
-                        else if (2 * k + 1 > q)
-                            F = fma(wl[kGtabNodeOff + R * 2 + slot], X.s[q0 + k][v] + X.s[q0 + q - 1 - k][v], F);
-                    } else {
-                        F = fma(wl[kGtabNodeOff + R * 2 + slot], X.s[q0 + k][v], F);
-                    }
-                    fl |= X.fl[q0 + k];
-                }
+        if (valid && side == 0) {
+            const real *qw = wl + kGtabNodeOff + R * 2;
+            real F;
+            if constexpr (HLL) {
+                // mirror-paired quadrature (see the first pass's y faces)
+                if (R <= 0) F = fma(qw[0], X.f[oct][0][v], real(0));
+                else if (R == 1) F = fma(qw[0], X.f[oct][1][v] + X.f[oct][0][v], real(0));
+                else F = fma(qw[0], X.f[oct][2][v] + X.f[oct][0][v], fma(qw[1], X.f[oct][1][v], real(0)));
+            } else {
+                F = fma(qw[0], X.f[oct][0][v], real(0));
+                if (R >= 1) F = fma(R >= 2 ? qw[1] : qw[0], X.f[oct][1][v], F);
+                if (R >= 2) F = fma(qw[0], X.f[oct][2][v], F);
             }
+            const uint8_t fl = (uint8_t)((ml ? 1 : 0) | (mr ? 2 : 0));
             if (dir == 0) {
                 A.FX[(size_t)v * nfx + fo] = F;
-                if (v == 0) A.FXf[fo] = (uint8_t)fl;
+                if (v == 0) A.FXf[fo] = fl;
             } else {
                 A.GY[(size_t)v * nfy + fo] = F;
-                if (v == 0) A.GYf[fo] = (uint8_t)fl;
+                if (v == 0) A.GYf[fo] = fl;
             }
         }
         wave_lds_sync();  // the next round overwrites X
@@ -724,165 +589,230 @@ __device__ __forceinline__ void faces_phase(const StageArgs<real> &A, const real
 // Cascade pass, part 2: re-evaluate the listed cells from the stored fluxes,
 // re-detect, lower the troubled ones and claim the faces and cells of the next
 // pass.  Detection reads no other cell's order, so lowering in place is safe.
-// Everything a cell needs (fluxes, flags, its radius-2 neighbourhood) is loaded
-// at once, up front.  The number of rounds is uniform across the wavefront.
+//
+// Four lanes per cell, for the same reason as the eight per face: lane w updates
+// variable w, holds the face neighbour w (west, east, south, north) with its pressure
+// and normal velocity, and claims face w and neighbour w; what the others need passes
+// by quad moves.  The candidate, the bounds and the verdict are the same in all four.
+// Every lane of the wavefront runs with a valid cell (lanes past the list repeat an
+// entry, store nothing and claim nothing), so the quad moves see no idle lane.
 //
 // cell_load gathers what does not depend on this pass's fluxes (the stage input
 // around the cell, U^n and its order); cell_finish reads the fluxes and flags,
 // forms the candidate, detects, writes the result and lowers.  The tail issues
 // cell_load while other wavefronts still recompute the faces.
-constexpr int kDi13[13] = {0, -1, 1, 0, 0, -2, 2, 0, 0, -1, 1, -1, 1};
-constexpr int kDj13[13] = {0, 0, 0, -1, 1, 0, 0, -2, 2, -1, -1, 1, 1};
-
 template <typename real>
 struct CellIn {
     int c, i, j, o;
-    real rho[13];     // radius-2 diamond of densities (kDi13, kDj13)
-    real mom[5][3];   // the other variables of the cell and its face neighbours
-    real un[4];       // U^n of the cell (stages 1, 2)
+    real us, un;   // U_s and U^n of the cell, variable w
+    real nb[4];    // face neighbour w
+    real r8[8];    // densities of the outer ring of the radius-2 diamond (kD13[5..12])
 };
 
 template <bool WALLS, typename real>
 __device__ __forceinline__ void cell_load(const StageArgs<real> &A, int c, CellIn<real> &X)
 {
-    const int nx = A.nx, ny = A.ny;
+    const int nx = A.nx, ny = A.ny, w = threadIdx.x & 3;
     const size_t plane = (size_t)nx * ny;
     X.c = c;
-    X.j = c / nx;
-    X.i = c - X.j * nx;
-    size_t yr[5];
-    int xc[5];
+    split_id(c, nx, A.inv_nx, X.i, X.j);
+    int xc[5], yr[5];
+    const bool out = near_cells(A, X.i, X.j, xc, yr);
+    const int di = w == 0 ? -1 : (w == 1 ? 1 : 0), dj = w == 2 ? -1 : (w == 3 ? 1 : 0);
+    const unsigned nbi = (unsigned)((w == 2 ? yr[1] : (w == 3 ? yr[3] : yr[2])) + (w == 0 ? xc[1] : (w == 1 ? xc[3] : xc[2])));
+    X.us = (A.Us + w * plane)[c];
 #pragma unroll
-    for (int d = 0; d < 5; ++d) {
-        yr[d] = (size_t)wrap<WALLS>(X.j + d - 2, ny, A.bcy) * nx;
-        xc[d] = wrap<WALLS>(X.i + d - 2, nx, A.bcx);
-    }
+    for (int u = 0; u < 4; ++u) X.nb[u] = (A.Us + u * plane)[nbi];
 #pragma unroll
-    for (int m = 0; m < 13; ++m) X.rho[m] = A.Us[yr[kDj13[m] + 2] + xc[kDi13[m] + 2]];
-#pragma unroll
-    for (int m = 0; m < 5; ++m)
-#pragma unroll
-        for (int w = 1; w < 4; ++w) X.mom[m][w - 1] = A.Us[w * plane + yr[kDj13[m] + 2] + xc[kDi13[m] + 2]];
+    for (int m = 0; m < 8; ++m) X.r8[m] = A.Us[(unsigned)(yr[kD13[5 + m][1] + 2] + xc[kD13[5 + m][0] + 2])];
+    X.un = A.s == 0 ? real(0) : (A.Un + w * plane)[c];
+    X.o = A.order[c];
     // reflecting walls reverse the normal momentum of a mirrored face neighbour;
     // an inflow slit's ghost cells hold the injected state
     if (WALLS) {
+        if (out) {
+            const int x = X.i + di, y = X.j + dj;
+            const int nx1 = (A.bcx == 2) & ((unsigned)x >= (unsigned)nx), ny1 = (A.bcy == 2) & ((unsigned)y >= (unsigned)ny);
+            X.nb[1] *= nx1 ? real(-1) : real(1);
+            X.nb[2] *= ny1 ? real(-1) : real(1);
+            if (A.slit) {
+                real sb[4], st[4];
 #pragma unroll
-        for (int m = 1; m < 5; ++m) {
-            X.mom[m][0] *= msign<real>(X.i + kDi13[m], nx, A.bcx == 2);
-            X.mom[m][1] *= msign<real>(X.j + kDj13[m], ny, A.bcy == 2);
-        }
-        if (A.slit) {
+                for (int u = 0; u < 4; ++u) {
+                    sb[u] = A.slitU[0][u];
+                    st[u] = A.slitU[1][u];
+                }
+                hold4(sb);
+                hold4(st);
+                const bool s = in_slit(A, x, y);
 #pragma unroll
-            for (int m = 1; m < 13; ++m) {
-                const bool s = in_slit(A, X.i + kDi13[m], X.j + kDj13[m]);
-                const int side = X.j + kDj13[m] < 0 ? 0 : 1;
-                X.rho[m] = s ? A.slitU[side][0] : X.rho[m];
-                if (m < 5)
+                for (int u = 0; u < 4; ++u) X.nb[u] = s ? (y < 0 ? sb[u] : st[u]) : X.nb[u];
 #pragma unroll
-                    for (int w = 1; w < 4; ++w) X.mom[m][w - 1] = s ? A.slitU[side][w] : X.mom[m][w - 1];
+                for (int m = 0; m < 8; ++m) {
+                    const int xm = X.i + kD13[5 + m][0], ym = X.j + kD13[5 + m][1];
+                    X.r8[m] = in_slit(A, xm, ym) ? (ym < 0 ? sb[0] : st[0]) : X.r8[m];
+                }
             }
         }
     }
-#pragma unroll
-    for (int w = 0; w < 4; ++w) X.un[w] = A.s == 0 ? real(0) : A.Un[w * plane + c];
-    X.o = A.order[c];
 }
 
-// The stored fluxes and Riemann-state flags of a cell's four faces (faces i-1/2,
-// i+1/2, j-1/2, j+1/2; fid: their face ids as the claims list them).
+// Returns whether the cell is troubled (it has then been lowered; the same in its four
+// lanes).  valid: this lane's cell is one of the list (else nothing is stored).
 template <typename real>
-struct CellFlux {
-    real f[4][4];  // [face][variable]
-    int fl[4];
-    int fid[4];
-};
-
-template <typename real>
-__device__ __forceinline__ void cell_fetch(const StageArgs<real> &A, const CellIn<real> &X, CellFlux<real> &F)
+__device__ __forceinline__ bool cell_finish(const StageArgs<real> &A, const CellIn<real> &X, real dt, bool valid)
 {
-    const int nx = A.nx, ny = A.ny;
+    const int nx = A.nx, ny = A.ny, w = threadIdx.x & 3;
+    const size_t plane = (size_t)nx * ny;
     const size_t nfx = (size_t)(nx + 1) * ny, nfy = (size_t)nx * (ny + 1);
-    const size_t fxm = (size_t)X.j * (nx + 1) + X.i, gym = (size_t)X.j * nx + X.i;  // faces i-1/2, j-1/2
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        F.f[0][w] = A.FX[w * nfx + fxm];
-        F.f[1][w] = A.FX[w * nfx + fxm + 1];
-        F.f[2][w] = A.GY[w * nfy + gym];
-        F.f[3][w] = A.GY[w * nfy + gym + nx];
-    }
-    F.fl[0] = A.FXf[fxm];
-    F.fl[1] = A.FXf[fxm + 1];
-    F.fl[2] = A.GYf[gym];
-    F.fl[3] = A.GYf[gym + nx];
-    F.fid[0] = (int)fxm;
-    F.fid[1] = (int)fxm + 1;
-    F.fid[2] = (int)(nfx + gym);
-    F.fid[3] = (int)(nfx + gym + nx);
-    // every flux and flag is consumed here: the flag loads are issued with the
-    // flux loads (not sunk into the branch of the detection that reads them), and
-    // the cell waits once for all of them
-    asm volatile("" ::"v"(F.fl[0]), "v"(F.fl[1]), "v"(F.fl[2]), "v"(F.fl[3]), "v"(F.f[0][0]), "v"(F.f[0][1]),
-                 "v"(F.f[0][2]), "v"(F.f[0][3]), "v"(F.f[1][0]), "v"(F.f[1][1]), "v"(F.f[1][2]), "v"(F.f[1][3]),
-                 "v"(F.f[2][0]), "v"(F.f[2][1]), "v"(F.f[2][2]), "v"(F.f[2][3]), "v"(F.f[3][0]), "v"(F.f[3][1]),
-                 "v"(F.f[3][2]), "v"(F.f[3][3]));
-}
-
-// Returns whether the cell is troubled (it has then been lowered).
-template <typename real>
-__device__ __forceinline__ bool cell_finish_flux(const StageArgs<real> &A, const CellIn<real> &X,
-                                                 const CellFlux<real> &F, real dt)
-{
-    const size_t plane = (size_t)A.nx * A.ny;
+    const unsigned fxm = (unsigned)(X.j * (nx + 1) + X.i), gym = (unsigned)(X.j * nx + X.i);  // faces i-1/2, j-1/2
+    const real *FX = A.FX + w * nfx, *GY = A.GY + w * nfy;
+    const real f0 = FX[fxm], f1 = FX[fxm + 1], f2 = GY[gym], f3 = GY[gym + (unsigned)nx];
+    int fl = (w < 2 ? A.FXf : A.GYf)[w == 0 ? fxm : (w == 1 ? fxm + 1 : (w == 2 ? gym : gym + (unsigned)nx))];
+    const real mine = X.us - dt * axis_sum(dv(f1 - f0, A.dx), dv(f3 - f2, A.dy));
+    if (valid) (A.Uout + w * plane)[X.c] = combine(A.s, X.un, mine, A.ca, A.cb);
     // an inadmissible state on either side of any of the cell's faces
-    const bool rs = (F.fl[0] | F.fl[1] | F.fl[2] | F.fl[3]) != 0;
-    real ust[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const real us = w == 0 ? X.rho[0] : X.mom[0][w - 1];
-        const real dFx = F.f[1][w] - F.f[0][w];
-        ust[w] = us - dt * axis_sum(dv(dFx, A.dx), dv(F.f[3][w] - F.f[2][w], A.dy));
+    fl |= dpp<0xb1>(fl);  // quad_perm:[1,0,3,2]
+    fl |= dpp<0x4e>(fl);  // quad_perm:[2,3,0,1]
+    const real rho = quad<0>(mine), mx = quad<1>(mine), my = quad<2>(mine), E = quad<3>(mine);
+    const real g = A.gamma;
+    // Detection (Steps 4-10), as troubled()
+    const real p = pressure(g, rho, mx, my, E);
+    const bool bad = !(finite(rho) && finite(p))             // Step 4: CAD
+                     || ((A.flags & 8u) && fl != 0)          // CAD on the Riemann states
+                     || !(rho > real(0) && p > real(0));     // Step 5: PAD
+    // DMP bounds over the cell and its face neighbours
+    const real rc = quad<0>(X.us), rW = quad<0>(X.nb[0]), rE = quad<1>(X.nb[0]), rS = quad<2>(X.nb[0]), rN = quad<3>(X.nb[0]);
+    real lo = rc, hi = rc;
+    lo = vmin(lo, rW); hi = vmax(hi, rW);
+    lo = vmin(lo, rE); hi = vmax(hi, rE);
+    lo = vmin(lo, rS); hi = vmax(hi, rS);
+    lo = vmin(lo, rN); hi = vmax(hi, rN);
+    bool open = X.o != 0 && !bad && !(lo <= rho && rho <= hi);                 // Step 10; Step 8: DMP
+    open = open && !((A.flags & 2u) && (hi - lo) < A.plat_thr);                // Step 7: plateau
+    if ((A.flags & 1u) && __any(open)) {                                       // Step 6: CSD
+        const real pn = pressure(g, X.nb[0], X.nb[1], X.nb[2], X.nb[3]);
+        const real un = dv(w < 2 ? X.nb[1] : X.nb[2], X.nb[0]);
+        // the x terms in lanes 0 and 1, the y terms in lanes 2 and 3
+        const real plo = dpp<0xa0>(pn), phi = dpp<0xf5>(pn);  // quad_perm:[0,0,2,2], [1,1,3,3]
+        const real ulo = dpp<0xa0>(un), uhi = dpp<0xf5>(un);
+        const real td = real(2) * (w < 2 ? A.dx : A.dy);
+        const real du = dv(uhi - ulo, td), dp = dv(fabs(phi - plo), td * vmin(phi, plo));
+        const real divV = quad<0>(du) + quad<2>(du), gradp = quad<0>(dp) + quad<2>(dp);
+        open = open && !(divV >= -A.sigma_v && gradp <= A.sigma_p);
     }
-    auto nb = [&](int di, int dj, int w) -> real {
-        int m = 0;
+    if ((A.flags & 4u) && __any(open)) {                                       // Step 9: u2
+        // lanes 0 and 2 take the curvatures in x, lanes 1 and 3 those in y
+        const bool y = (w & 1) != 0;
+        const real w0 = y ? A.W.curv[1][0] : A.W.curv[0][0], wa = y ? A.W.curv[1][1] : A.W.curv[0][1];
+        const real wt = y ? A.W.curv[1][2] : A.W.curv[0][2];
+        const real rho5[5] = {rc, rW, rE, rS, rN};
+        // sums of the x pair and the y pair around the cell and its face neighbours
+        const real sx[5] = {rW + rE, X.r8[0] + rc, rc + X.r8[1], X.r8[4] + X.r8[5], X.r8[6] + X.r8[7]};
+        const real sy[5] = {rS + rN, X.r8[4] + X.r8[6], X.r8[5] + X.r8[7], X.r8[2] + rc, rc + X.r8[3]};
+        real cmin = real(0), cmax = real(0);
 #pragma unroll
-        for (int t = 0; t < 13; ++t)
-            if (kDi13[t] == di && kDj13[t] == dj) m = t;
-        return w == 0 ? X.rho[m] : X.mom[m < 5 ? m : 0][w - 1];
-    };
-    const bool tr = troubled(A, X.o, ust, rs, nb);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) A.Uout[w * plane + X.c] = combine(A.s, X.un[w], ust[w], A.ca, A.cb);
-    if (tr) A.order[X.c] = (uint8_t)next_radius(A.next[0], A.next[1], A.next[2], A.next[3], X.o);
+        for (int m = 0; m < 5; ++m) {
+            real kap = w0 * rho5[m];
+            kap = fma(wa, y ? sy[m] : sx[m], kap);
+            kap = fma(wt, y ? sx[m] : sy[m], kap);
+            cmin = m == 0 ? kap : vmin(cmin, kap);
+            cmax = m == 0 ? kap : vmax(cmax, kap);
+        }
+        const bool prod = cmin * cmax > -A.delta;
+        const bool a = prod && vmax(fabs(cmax), fabs(cmin)) < A.delta;
+        const bool b = prod && fabs(cmin) >= real(0.5) * fabs(cmax);
+        const int ok = (a || b) ? 1 : 0;
+        open = open && !(quad<0>(ok) != 0 && quad<1>(ok) != 0);
+    }
+    const bool tr = valid && X.o != 0 && (bad || open);
+    if (tr && w == 0) A.order[X.c] = (uint8_t)next_radius(A.next[0], A.next[1], A.next[2], A.next[3], X.o);
     return tr;
 }
 
+// Claims after lowering cell (i, j) (act: this quad's cell was lowered): its four faces
+// (and, on periodic axes, the duplicate copy of a boundary face) are listed for
+// recomputation in the next pass, and the cell with its four face neighbours for
+// re-evaluation; *P.tcount counts the lowered cells (null: not counted).  A stamp per face and per
+// cell keeps each list duplicate-free.  Lane w of the quad claims face w (x faces i,
+// i + 1 of row j; y faces j, j + 1 of column i) and face neighbour w, lane 0 the cell
+// itself, lanes 1 and 2 the duplicates: three atomics a lane in flight together, list
+// slots from ballots and one reservation per wavefront and list.  Must be reached by all
+// 64 lanes of the wavefront together.
 template <typename real>
-__device__ __forceinline__ bool cell_finish(const StageArgs<real> &A, const CellIn<real> &X, real dt)
+__device__ __forceinline__ void claim_after_lowering(const StageArgs<real> &A, const PassOut &P, int i, int j,
+                                                     bool act)
 {
-    CellFlux<real> F;
-    cell_fetch(A, X, F);
-    return cell_finish_flux(A, X, F, dt);
+    const unsigned long long any = __ballot(act);
+    if (any == 0ull) return;
+    const int nx = A.nx, ny = A.ny, lane = threadIdx.x & 63, w = lane & 3;
+    const int nfx = (nx + 1) * ny;
+    const int fx = j * (nx + 1) + i, gy = nfx + j * nx + i;
+    const int fid = w == 0 ? fx : (w == 1 ? fx + 1 : (w == 2 ? gy : gy + nx));
+    const int ii = i + (w == 0 ? -1 : (w == 1 ? 1 : 0)), jj = j + (w == 2 ? -1 : (w == 3 ? 1 : 0));
+    const bool cok = (A.bcx == 0 || (ii >= 0 && ii < nx)) && (A.bcy == 0 || (jj >= 0 && jj < ny));
+    // (on a non-periodic axis only in-domain indices get here: no mirror needed)
+    const int cid = wrap(jj, ny, A.bcy) * nx + wrap(ii, nx, A.bcx);
+    // lane 1: the copy of x face 0 / face nx; lane 2: of y face 0 / face ny
+    const bool dup = (w == 1 && A.bcx == 0 && (i == 0 || i == nx - 1)) || (w == 2 && A.bcy == 0 && (j == 0 || j == ny - 1));
+    const int did = w == 1 ? j * (nx + 1) + (i == 0 ? nx : 0) : nfx + (j == 0 ? ny * nx : 0) + i;
+    unsigned a0 = P.stamp, a1 = P.stamp, a2 = P.stamp;
+    if (act) {
+        a0 = atomicMax(&A.fstamp[fid], P.stamp);
+        if (cok) a1 = atomicMax(&A.cstamp[cid], P.stamp);
+        if (w == 0) a2 = atomicMax(&A.cstamp[j * nx + i], P.stamp);
+        else if (dup) a2 = atomicMax(&A.fstamp[did], P.stamp);
+    }
+    const bool m0 = a0 < P.stamp, m1 = a1 < P.stamp, m2 = a2 < P.stamp;  // newly claimed here
+    const unsigned long long bf0 = __ballot(m0), bc1 = __ballot(m1), bf2 = __ballot(m2 && w != 0), bc2 = __ballot(m2 && w == 0);
+    const int nf0 = __popcll(bf0), nc1 = __popcll(bc1);
+    int fb = 0, cb = 0;
+    if (lane == 0) {
+        fb = atomicAdd(P.fcount, nf0 + __popcll(bf2));
+        cb = atomicAdd(P.ccount, nc1 + __popcll(bc2));
+        if (P.tcount) atomicAdd(P.tcount, __popcll(any) >> 2);
+    }
+    fb = __builtin_amdgcn_readfirstlane(fb);
+    cb = __builtin_amdgcn_readfirstlane(cb);
+    if (m0) P.flist[fb + below(bf0)] = fid;
+    if (m1) P.clist[cb + below(bc1)] = cid;
+    if (m2 && w == 0) P.clist[cb + nc1 + below(bc2)] = j * nx + i;
+    if (m2 && w != 0) P.flist[fb + nf0 + below(bf2)] = did;
 }
 
 template <bool WALLS, typename real>
-__device__ __forceinline__ void cells_phase(const StageArgs<real> &A, const int *clist, int n, int t0, int stride,
+__device__ __forceinline__ void cells_phase(const StageArgs<real> &A, const int *clist, int n, int slot, int per,
                                             const PassOut &P, real dt, int pre = 0, bool use_pre = false)
 {
-    const int nround = (n + stride - 1) / stride;
-    for (int r = 0; r < nround; ++r) {
-        const int idx = r * stride + t0;
+    for (int base = 0; base < n; base += per) {
+        const int idx = base + slot;
+        if (__builtin_amdgcn_readfirstlane(idx) >= n) break;  // nothing (more) for this wavefront
         const bool valid = idx < n;
-        bool tr = false;
+        CellIn<real> X;
+        cell_load<WALLS>(A, (use_pre && base == 0) ? pre : clist[valid ? idx : n - 1], X);
+        const bool tr = cell_finish(A, X, dt, valid);
+        claim_after_lowering(A, P, X.i, X.j, tr);
+    }
+}
+
+// The claims of the cells the first pass lowered (listed in low, count *nlow):
+// the same claims, stamps and lists as if they had been made in the pass.
+template <typename real>
+__global__ __launch_bounds__(256) void k_claims_first(const StageArgs<real> A, const PassOut P, const int *low,
+                                                      const int *nlow)
+{
+    const int n = *nlow;
+    PassOut Q = P;
+    Q.stamp = *A.stamp0;
+    Q.tcount = nullptr;  // the first pass has counted them
+    const int stride = gridDim.x * blockDim.x;
+    const int nround = (4 * n + stride - 1) / stride;
+    for (int r = 0; r < nround; ++r) {
+        const int t = (r * stride + blockIdx.x * blockDim.x + threadIdx.x) >> 2;
+        const bool act = t < n;
         int i = 0, j = 0;
-        if (valid) {
-            CellIn<real> X;
-            cell_load<WALLS>(A, (use_pre && r == 0) ? pre : clist[idx], X);
-            tr = cell_finish(A, X, dt);
-            i = X.i;
-            j = X.j;
-        }
-        wave_count(tr, P.tcount);
-        claim_after_lowering(A, P, i, j, tr);
+        if (act) split_id(low[t], A.nx, A.inv_nx, i, j);
+        claim_after_lowering(A, Q, i, j, act);
     }
 }
 
@@ -907,15 +837,16 @@ __device__ __forceinline__ bool pass_runs(const Cascade &C, int k)
 }
 
 template <typename real, bool WALLS, bool HLL>
-__global__ __launch_bounds__(256) void k_faces(const StageArgs<real> A, const Cascade C, int k)
+__global__ __launch_bounds__(256) void k_faces(const StageArgs<real>, const Cascade C, int k)
 {
+    const StageArgs<real> &A = first_arg<StageArgs<real>>();
     __shared__ real wl[kGtabSize];
     __shared__ FaceXchg<real> xch[4];
     const int cap = (A.nx + 1) * A.ny + A.nx * (A.ny + 1);
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
     // issued together, before the counts are known: this thread's first list
     // entry (in bounds; used only if the pass runs and covers it) and the weights
-    const int i0 = t0 >> 2;
+    const int i0 = t0 >> 3;
     const int pre = C.flist[k & 1][i0 < cap ? i0 : cap - 1];
     load_gtab<256>(A.gtab, wl);
     if (!pass_runs(C, k)) {
@@ -924,24 +855,27 @@ __global__ __launch_bounds__(256) void k_faces(const StageArgs<real> A, const Ca
     }
     int n = C.ctl->nface[k];
     n = n < cap ? n : cap;  // a list holds each face at most once
-    if (4 * n <= (int)(blockIdx.x * blockDim.x)) return;  // no face for this block
+    if (n <= (int)(blockIdx.x * 32)) return;  // no face for this block
     __syncthreads();
-    faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n, t0, gridDim.x * blockDim.x, pre, true);
+    faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n, i0, gridDim.x * 32, pre, true);
 }
 
 template <typename real, bool WALLS>
-__global__ __launch_bounds__(64) void k_cells(const StageArgs<real> A, const Cascade C, int k)
+__global__ __launch_bounds__(256) void k_cells(const StageArgs<real>, const Cascade C, int k)
 {
+    const StageArgs<real> &A = first_arg<StageArgs<real>>();
     const int cap = A.nx * A.ny;
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
-    // this thread's first list entry, issued before the counts are known (in bounds)
-    const int pre = C.clist[k & 1][t0 < cap ? t0 : cap - 1];
+    // this quad's first list entry, issued before the counts are known (in bounds; a
+    // list only ever holds cells of the grid)
+    const int i0 = t0 >> 2;
+    const int pre = C.clist[k & 1][i0 < cap ? i0 : cap - 1];
     const real dt = (real)(*A.dt * A.dtf);
     if (!pass_runs(C, k)) return;
     int n = C.ctl->ncell[k];
     n = n < cap ? n : cap;  // a list holds each cell at most once
-    if (n <= (int)(blockIdx.x * blockDim.x)) return;
-    cells_phase<WALLS>(A, C.clist[k & 1], n, t0, gridDim.x * blockDim.x, pass_out(C, k, C.ctl->stamp0), dt, pre, true);
+    if (n <= (int)(blockIdx.x * 64)) return;
+    cells_phase<WALLS>(A, C.clist[k & 1], n, i0, gridDim.x * 64, pass_out(C, k, C.ctl->stamp0), dt, pre, true);
 }
 
 // The tail of a long cascade (few troubled cells per pass) in one workgroup:
@@ -950,22 +884,19 @@ __global__ __launch_bounds__(64) void k_cells(const StageArgs<real> A, const Cas
 // kend is reached, or the previous evaluation left more than back_thr troubled
 // cells (hand back to the multi-block passes).  The counts of the running passes
 // stay in LDS and are copied to the control block as each pass completes.
-// Threads of the tail workgroup: 512 (two wavefronts per SIMD, at most 256
-// registers a lane); 256 in the FP64 build for walls and slits, whose cell and
-// face state needs more than 256 registers (one wavefront per SIMD gives it 512,
-// with no spill to scratch).
-template <typename real, bool WALLS>
+// Threads of the tail workgroup: as many as its registers allow (four wavefronts per SIMD
+// in FP32, three in FP64).
+template <typename real>
 constexpr int tail_threads()
 {
-    return sizeof(real) == 8 && WALLS ? 256 : 512;
+    return sizeof(real) == 8 ? 768 : 1024;
 }
-constexpr int kTailMaxWaves = 8;
 
 // LDS of the single-workgroup cascade.
 template <typename real>
 struct TailShared {
     real wl[kGtabSize];
-    FaceXchg<real> xch[kTailMaxWaves];
+    FaceXchg<real> xch[tail_threads<real>() / 64];
     int cnt[2][3];  // [pass parity][faces, cells, troubled cells of the previous evaluation]
     int kfirst;
 };
@@ -978,7 +909,7 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
     Ctl *ctl = C.ctl;
     const unsigned stamp0 = ctl->stamp0;
     const real dtr = (real)(*A.dt * A.dtf);  // read once, not after each pass's barrier
-    load_gtab<tail_threads<real, WALLS>()>(A.gtab, S.wl);
+    load_gtab<tail_threads<real>()>(A.gtab, S.wl);
     int k0 = ctl->tail_k0 > 0 ? ctl->tail_k0 : kdef;
     if (ctl->tail_k0 <= 0 && kbeg < kdef) {
         // no hand-over: the cascade either ended inside the batch kbeg..kdef-1 (at
@@ -1021,31 +952,24 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
         P.fcount = &S.cnt[(k + 1) & 1][0];
         P.ccount = &S.cnt[(k + 1) & 1][1];
         P.tcount = &S.cnt[(k + 1) & 1][2];
-        const int fw = (4 * nf + 63) >> 6, cw = (nc + 63) >> 6;  // wavefronts of faces, of cells
+        const int fw = (8 * nf + 63) >> 6, cw = (4 * nc + 63) >> 6;  // wavefronts of faces, of cells
         const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // uniform per wavefront
-        if (fw + cw <= tail_threads<real, WALLS>() / 64) {
+        if (fw + cw <= tail_threads<real>() / 64) {
             // one round each, on separate wavefronts: the cell wavefronts gather
             // their inputs while the face wavefronts recompute the fluxes
-            const int c0 = tail_threads<real, WALLS>() / 64 - cw;  // first cell wavefront
+            const int c0 = tail_threads<real>() / 64 - cw;  // first cell wavefront
             const bool cellwave = wv >= c0;
-            const int idx = (int)threadIdx.x - 64 * c0;
-            const bool valid = cellwave && idx < nc;
+            const int idx = ((int)threadIdx.x - 64 * c0) >> 2;
             CellIn<real> X;
-            X.i = X.j = 0;
-            if (valid) cell_load<WALLS>(A, C.clist[k & 1][idx], X);
-            if (!cellwave && wv < fw)
-                faces_phase<WALLS, HLL>(A, S.wl, S.xch[wv], C.flist[k & 1], nf, threadIdx.x, 64 * fw);
+            if (cellwave) cell_load<WALLS>(A, C.clist[k & 1][idx < nc ? idx : nc - 1], X);
+            else if (wv < fw)
+                faces_phase<WALLS, HLL>(A, S.wl, S.xch[wv], C.flist[k & 1], nf, threadIdx.x >> 3, 8 * fw);
             __syncthreads();
-            if (cellwave) {
-                bool tr = false;
-                if (valid) tr = cell_finish(A, X, dtr);
-                wave_count(tr, P.tcount);
-                claim_after_lowering(A, P, X.i, X.j, tr);
-            }
+            if (cellwave) claim_after_lowering(A, P, X.i, X.j, cell_finish(A, X, dtr, idx < nc));
         } else {
-            faces_phase<WALLS, HLL>(A, S.wl, S.xch[wv], C.flist[k & 1], nf, threadIdx.x, blockDim.x);
+            faces_phase<WALLS, HLL>(A, S.wl, S.xch[wv], C.flist[k & 1], nf, threadIdx.x >> 3, tail_threads<real>() / 8);
             __syncthreads();
-            cells_phase<WALLS>(A, C.clist[k & 1], nc, threadIdx.x, blockDim.x, P, dtr);
+            cells_phase<WALLS>(A, C.clist[k & 1], nc, threadIdx.x >> 2, tail_threads<real>() / 4, P, dtr);
         }
     }
     if (k >= kend) {
@@ -1065,9 +989,10 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
 }
 
 template <typename real, bool WALLS, bool HLL>
-__global__ __launch_bounds__((tail_threads<real, WALLS>())) void k_tail(const StageArgs<real> A, const Cascade C, int kbeg, int kdef,
+__global__ __launch_bounds__((tail_threads<real>())) void k_tail(const StageArgs<real>, const Cascade C, int kbeg, int kdef,
                                                        int kend)
 {
+    const StageArgs<real> &A = first_arg<StageArgs<real>>();
     __shared__ TailShared<real> S;
     tail_body<WALLS, HLL>(A, C, kbeg, kdef, kend, S);
 }
@@ -1320,11 +1245,11 @@ __global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k_first_pass_ba
 // every problem's share of the pass (0 when it has no work, or when its previous
 // evaluation left at most tail_thr troubled cells, which then leaves the rest of
 // its cascade to its tail workgroup) and lays the shares end to end: plan[p] is
-// the first work block of problem p, in units of 64 faces (256 threads) and,
-// at plan + nprob + 1, of 64 cells.  The pass kernels have a fixed grid whose
+// the first work block of problem p, in units of 32 faces and, at plan + nprob + 1, of
+// 64 cells (256 threads each).  The pass kernels have a fixed grid whose
 // blocks stride over these work blocks, so the whole batch's faces and cells of a
 // pass are spread over the GPU however they fall among the problems.  Pass 0 is
-// the claims of the cells the first passes lowered (64 x 4 cells per block).
+// the claims of the cells the first passes lowered (64 cells per block).
 constexpr int kBatchPasses = 12;
 constexpr int kBatchFaceGrid = 1024, kBatchCellGrid = 2048;
 
@@ -1341,11 +1266,11 @@ __global__ __launch_bounds__(1024) void k_batch_plan(const BatchTabs<real> B, in
             const StageArgs<real> &A = table_entry(B.args, p);
             const Cascade &C = table_entry(B.casc, p);
             if (k == 0) {
-                df = (C.ctl->nlow + 255) / 256;
+                df = (C.ctl->nlow + 63) / 64;
             } else if (pass_runs(C, k)) {
                 const int capf = (A.nx + 1) * A.ny + A.nx * (A.ny + 1), capc = A.nx * A.ny;
                 const int nf = min(C.ctl->nface[k], capf), nc = min(C.ctl->ncell[k], capc);
-                df = (nf + 63) / 64;
+                df = (nf + 31) / 32;
                 dc = (nc + 63) / 64;
             } else if (C.ctl->ncell[k] > 0) {
                 C.ctl->tail_k0 = k;  // the tail takes over from this pass
@@ -1392,14 +1317,11 @@ __global__ __launch_bounds__(256) void k_claims_first_batch(const BatchTabs<real
         const Cascade &C = table_entry(B.casc, p);
         PassOut P = table_entry(B.pout, p);
         P.stamp = *A.stamp0;
-        const int t = (w - pl[p]) * 256 + (int)threadIdx.x;
+        P.tcount = nullptr;  // the first pass has counted them
+        const int t = ((w - pl[p]) * 256 + (int)threadIdx.x) >> 2;
         const bool act = t < C.ctl->nlow;
         int i = 0, j = 0;
-        if (act) {
-            const int c = C.clist[0][t];
-            j = c / A.nx;
-            i = c - j * A.nx;
-        }
+        if (act) split_id(C.clist[0][t], A.nx, A.inv_nx, i, j);
         claim_after_lowering(A, P, i, j, act);
     }
 }
@@ -1424,13 +1346,13 @@ __global__ __launch_bounds__(256) void k_faces_batch(const BatchTabs<real> B, in
         }
         const int capf = (A.nx + 1) * A.ny + A.nx * (A.ny + 1);
         const int n = min(C.ctl->nface[k], capf);
-        faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n, (w - pl[p]) * 256 + (int)threadIdx.x,
-                                4 * n);
+        faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n,
+                                (w - pl[p]) * 32 + ((int)threadIdx.x >> 3), n);
     }
 }
 
 template <typename real, bool WALLS>
-__global__ __launch_bounds__(64) void k_cells_batch(const BatchTabs<real> B, int k, const int *plan)
+__global__ __launch_bounds__(256) void k_cells_batch(const BatchTabs<real> B, int k, const int *plan)
 {
     cptr<int> pl = (cptr<int>)(plan + B.nprob + 1);
     const int total = pl[B.nprob];
@@ -1439,7 +1361,7 @@ __global__ __launch_bounds__(64) void k_cells_batch(const BatchTabs<real> B, int
         const StageArgs<real> &A = table_entry(B.args, p);
         const Cascade &C = table_entry(B.casc, p);
         const int n = min(C.ctl->ncell[k], A.nx * A.ny);
-        cells_phase<WALLS>(A, C.clist[k & 1], n, (w - pl[p]) * 64 + (int)threadIdx.x, n,
+        cells_phase<WALLS>(A, C.clist[k & 1], n, (w - pl[p]) * 64 + ((int)threadIdx.x >> 2), n,
                            pass_out(C, k, C.ctl->stamp0), (real)(*A.dt * A.dtf));
     }
 }
@@ -1447,7 +1369,7 @@ __global__ __launch_bounds__(64) void k_cells_batch(const BatchTabs<real> B, int
 // Problem p = blockIdx.x runs the rest of its cascade in one workgroup, from the
 // pass the multi-block passes left to it (no hand-back).
 template <typename real, bool WALLS, bool HLL>
-__global__ __launch_bounds__((tail_threads<real, WALLS>())) void k_tail_batch(const BatchTabs<real> B)
+__global__ __launch_bounds__((tail_threads<real>())) void k_tail_batch(const BatchTabs<real> B)
 {
     __shared__ TailShared<real> S;
     const int p = blockIdx.x;
@@ -1535,10 +1457,10 @@ static hipError_t launch_batch_cascade(const BatchTabs<real> &B, hipStream_t st)
         hipLaunchKernelGGL(k_batch_plan<real>, dim3(1), dim3(1024), 0, st, B, k, B.plan);
         hipLaunchKernelGGL((k_faces_batch<real, WALLS, HLL>), dim3(kBatchFaceGrid), dim3(256), 0, st, B, k,
                            (const int *)B.plan);
-        hipLaunchKernelGGL((k_cells_batch<real, WALLS>), dim3(kBatchCellGrid), dim3(64), 0, st, B, k,
+        hipLaunchKernelGGL((k_cells_batch<real, WALLS>), dim3(kBatchCellGrid), dim3(256), 0, st, B, k,
                            (const int *)B.plan);
     }
-    hipLaunchKernelGGL((k_tail_batch<real, WALLS, HLL>), dim3(B.nprob), dim3(tail_threads<real, WALLS>()), 0, st, B);
+    hipLaunchKernelGGL((k_tail_batch<real, WALLS, HLL>), dim3(B.nprob), dim3(tail_threads<real>()), 0, st, B);
     return hipGetLastError();
 }
 
@@ -1679,9 +1601,9 @@ hipError_t launch_cascade_pass(const StageArgs<real> &A, const Cascade &C, int k
     else
         hipLaunchKernelGGL((k_faces<real, false, false>), dim3(nblocks), dim3(256), 0, st, A, C, k);
     if (walls)
-        hipLaunchKernelGGL((k_cells<real, true>), dim3(nblocks), dim3(64), 0, st, A, C, k);
+        hipLaunchKernelGGL((k_cells<real, true>), dim3(nblocks), dim3(256), 0, st, A, C, k);
     else
-        hipLaunchKernelGGL((k_cells<real, false>), dim3(nblocks), dim3(64), 0, st, A, C, k);
+        hipLaunchKernelGGL((k_cells<real, false>), dim3(nblocks), dim3(256), 0, st, A, C, k);
     return hipGetLastError();
 }
 
@@ -1691,13 +1613,13 @@ hipError_t launch_cascade_tail(const StageArgs<real> &A, const Cascade &C, int k
 {
     const bool walls = A.bcx == 2 || A.bcy == 2 || A.slit != 0;
     if (walls && A.solver == 1)
-        hipLaunchKernelGGL((k_tail<real, true, true>), dim3(1), dim3(tail_threads<real, true>()), 0, st, A, C, kbeg, kdef, kend);
+        hipLaunchKernelGGL((k_tail<real, true, true>), dim3(1), dim3(tail_threads<real>()), 0, st, A, C, kbeg, kdef, kend);
     else if (walls)
-        hipLaunchKernelGGL((k_tail<real, true, false>), dim3(1), dim3(tail_threads<real, true>()), 0, st, A, C, kbeg, kdef, kend);
+        hipLaunchKernelGGL((k_tail<real, true, false>), dim3(1), dim3(tail_threads<real>()), 0, st, A, C, kbeg, kdef, kend);
     else if (A.solver == 1)
-        hipLaunchKernelGGL((k_tail<real, false, true>), dim3(1), dim3(tail_threads<real, false>()), 0, st, A, C, kbeg, kdef, kend);
+        hipLaunchKernelGGL((k_tail<real, false, true>), dim3(1), dim3(tail_threads<real>()), 0, st, A, C, kbeg, kdef, kend);
     else
-        hipLaunchKernelGGL((k_tail<real, false, false>), dim3(1), dim3(tail_threads<real, false>()), 0, st, A, C, kbeg, kdef, kend);
+        hipLaunchKernelGGL((k_tail<real, false, false>), dim3(1), dim3(tail_threads<real>()), 0, st, A, C, kbeg, kdef, kend);
     return hipGetLastError();
 }
 
