@@ -8,11 +8,13 @@
 // terms, u2 per direction), SSP-RK3 (eq. (rk3)), FP64 CFL dt.
 //
 // Kernels:
-//   k3_faces  one thread per face: both cells' node states at the face's EDP_1
-//             radius (dot products with the quad-precision weights), q^2 HLLC
-//             solves, the Gauss sum; flux and Riemann-state flags stored.  The
-//             first pass runs every face at the top radius, cascade passes the
-//             claimed faces.
+//   k3_faces_x, k3_faces_march  the first evaluation at radius 2: every face, a cell's
+//             ball read once for its two faces on the axis (k3_faces_top: radius 1, one
+//             thread per face).
+//   k3_faces  the claimed faces of a cascade pass, one thread per face: both cells' node
+//             states at the face's EDP_1 radius (dot products with the quad-precision
+//             weights), q^2 HLLC solves, the Gauss sum; flux and Riemann-state flags
+//             stored.
 //   k3_cells  one thread per cell: candidate from the six stored fluxes,
 //             detection, RK combination, lowering and claims (stamps, one atomic
 //             per wavefront and list) of the faces and cells of the next pass.
@@ -59,6 +61,14 @@ struct Stage3 {
     real curv[3][4];
     const unsigned *stamp0;
 };
+
+typedef const __attribute__((address_space(1))) char *global_bytes;
+
+// Index of (a, b), |a| + |b| <= 2, among the 13 offsets of the ball off one axis.
+__host__ __device__ constexpr int disc_index(int a, int b)
+{
+    return a == -2 ? 0 : (a == -1 ? 2 + b : (a == 0 ? 6 + b : (a == 1 ? 10 + b : 12)));
+}
 
 struct PassOut3 {
     int *flist, *fcount, *clist, *ccount, *tcount;
@@ -282,7 +292,7 @@ __global__ __launch_bounds__(128, 1) void k3_faces_top(const Stage3<real> S)
     S.Ff[A][loc] = (uint8_t)((bl ? 1 : 0) | (br ? 2 : 0));
 }
 
-// Radius 2 in the parity basis: one thread per face; per variable, each side's 25
+// Radius 2 in the parity basis: per variable, a cell's 25
 // ball values are folded into the 25 parity entries of the face axis (kPar3) and
 // the nine node states come from the four node classes' weights: 14 products for
 // the centre, 19 for each pair on a tangential axis, 25 for the four corners (77,
@@ -326,129 +336,355 @@ __device__ __forceinline__ void par3_entries(const real (&q)[25], real (&P)[kNPa
     }
 }
 
-// The nine node states (table order) of one face side from its parity entries.
+// Keeps values where they are computed: without it instruction selection moves the
+// products past the next group's weight loads.
+template <int N, typename real>
+__device__ __forceinline__ void hold(real (&x)[N])
+{
+#pragma unroll
+    for (int m = 0; m < N; ++m) asm volatile("" : "+v"(x[m]));
+}
+
+// Sum of the entries E0..E1-1 with weights w[0..]; the products in order of the entry.
+template <int E0, int E1, typename real>
+__device__ __forceinline__ real par3_dot(const real *w, const real (&P)[kNPar3])
+{
+    real s = real(0);
+#pragma unroll
+    for (int e = E0; e < E1; ++e) s = fma(w[e], P[e], s);
+    return s;
+}
+
+// The nine node states (table order) of one face side from its parity entries.  The
+// 77 weights are read through the scalar path, all at once in FP32 and in two lots in
+// FP64 (66 and 88 scalar registers), and given up before the next are read.
 template <typename real>
 __device__ __forceinline__ void par3_states(const real (&P)[kNPar3], cptr<real> W, real (&s)[9])
 {
-    real c0 = real(0), a1 = real(0), a2 = real(0), a3 = real(0);
+    constexpr int EE = kPar3EE, OE = EE + kPar3OE, EO = OE + kPar3EO;
+    real w[4][kNPar3];
+    auto load = [&](int cls) {
+        const cptr<real> Wc = W;
 #pragma unroll
-    for (int e = 0; e < kPar3EE; ++e) {
-        c0 = fma(W[e], P[e], c0);
-        a1 = fma(W[kNPar3 + e], P[e], a1);
-        a2 = fma(W[2 * kNPar3 + e], P[e], a2);
-        a3 = fma(W[3 * kNPar3 + e], P[e], a3);
+        for (int e = 0; e < kNPar3; ++e) w[cls][e] = Wc[cls * kNPar3 + e];
+    };
+    W = reread(W);
+    load(0);
+    load(1);
+    if constexpr (sizeof(real) == 4) {
+        load(2);
+        load(3);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    real b1 = real(0), b3 = real(0);
-#pragma unroll
-    for (int e = kPar3EE; e < kPar3EE + kPar3OE; ++e) {
-        b1 = fma(W[kNPar3 + e], P[e], b1);
-        b3 = fma(W[3 * kNPar3 + e], P[e], b3);
+    real x[4];
+    x[0] = par3_dot<0, EE>(w[0], P);
+    x[1] = par3_dot<0, EE>(w[1], P);
+    x[2] = par3_dot<EE, OE>(w[1], P);
+    x[3] = real(0);
+    if constexpr (sizeof(real) == 8) {
+        hold(x);
+        __builtin_amdgcn_sched_barrier(0);
+        W = reread(W);
+        load(2);
+        load(3);
     }
-    real c2 = real(0), c3 = real(0);
-#pragma unroll
-    for (int e = kPar3EE + kPar3OE; e < kNPar3 - 1; ++e) {
-        c2 = fma(W[2 * kNPar3 + e], P[e], c2);
-        c3 = fma(W[3 * kNPar3 + e], P[e], c3);
-    }
-    const real d3 = W[3 * kNPar3 + kNPar3 - 1] * P[kNPar3 - 1];
-    s[4] = c0;
-    s[1] = a1 + b1;
-    s[7] = a1 - b1;
+    s[4] = x[0];
+    s[1] = x[1] + x[2];
+    s[7] = x[1] - x[2];
+    const real a2 = par3_dot<0, EE>(w[2], P), c2 = par3_dot<OE, EO>(w[2], P);
     s[3] = a2 + c2;
     s[5] = a2 - c2;
+    const real a3 = par3_dot<0, EE>(w[3], P), b3 = par3_dot<EE, OE>(w[3], P), c3 = par3_dot<OE, EO>(w[3], P);
+    const real d3 = w[3][kNPar3 - 1] * P[kNPar3 - 1];
     s[0] = (a3 + b3) + (c3 + d3);
     s[2] = (a3 + b3) - (c3 + d3);
     s[6] = (a3 - b3) + (c3 - d3);
     s[8] = (a3 - b3) - (c3 - d3);
+    hold(s);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// Node states of both sides of face (i, j, k) of axis A (left cell (iL, jL, kL)).
-// IN: both balls lie inside the grid (offsets from the cell index, no mapping).
-template <int A, bool IN, typename real>
-__device__ __forceinline__ void top2_states(const Stage3<real> &S, int i, int j, int k, real (&sl)[9][5],
-                                            real (&sr)[9][5])
+// The lane's byte offsets into a variable are 32-bit (OFF), so that a load takes a scalar
+// base and one register: held in place by hold(), widened outside a loop they cost an add
+// and a register each.
+template <typename real, typename OFF, int N, typename Sel, typename Base>
+__device__ __forceinline__ void ball3(OFF (&off)[N], real (&q)[25], Base base, Sel sel)
 {
-    const size_t plane = (size_t)S.n[0] * S.n[1] * S.n[2];
-    const int iL = i - (A == 0), jL = j - (A == 1), kL = k - (A == 2);
-    const int sy = S.n[0], sz = S.n[0] * S.n[1];
-    const cptr<real> WL = (cptr<real>)S.pz + (2 * A + 1) * 4 * kNPar3;  // + face of the left cell
-    const cptr<real> WR = (cptr<real>)S.pz + (2 * A) * 4 * kNPar3;      // - face of the right cell
+    hold(off);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        // one variable's loads at a time: the node states of all five stay live
-        __builtin_amdgcn_sched_barrier(0);
-        const real *U = S.Us + v * plane;
-        // the weights are reloaded (scalar loads) for each variable rather than
-        // held in scalar registers across all five
-        cptr<real> WLv = WL, WRv = WR;
-        asm volatile("" : "+s"(WLv), "+s"(WRv));
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            const int ci = side == 0 ? iL : i, cj = side == 0 ? jL : j, ck = side == 0 ? kL : k;
-            real q[25], P[kNPar3], st[9];
-            if constexpr (IN) {
-                const real *c0 = U + ((size_t)ck * S.n[1] + cj) * S.n[0] + ci;
-#pragma unroll
-                for (int m = 0; m < 25; ++m) q[m] = c0[kBall[m][2] * sz + kBall[m][1] * sy + kBall[m][0]];
-            } else {
-#pragma unroll
-                for (int m = 0; m < 25; ++m) q[m] = U[cell3(S, ci + kBall[m][0], cj + kBall[m][1], ck + kBall[m][2])];
-            }
-            par3_entries<A>(q, P);
-            par3_states(P, side == 0 ? WLv : WRv, st);
-#pragma unroll
-            for (int n = 0; n < 9; ++n) {
-                if (side == 0) sl[n][v] = st[n];
-                else sr[n][v] = st[n];
-            }
-        }
-    }
+    for (int m = 0; m < 25; ++m)
+        q[m] = *(const __attribute__((address_space(1))) real *)(base(m) + off[sel(m)]);
 }
 
-template <typename real, int A>
-__global__ __launch_bounds__(128) void k3_faces_top2(const Stage3<real> S)
+// The nine HLLC solves of a face and their Gauss sum; left(n, sl) gives node n's left state.
+template <int A, typename real, typename Left>
+__device__ __forceinline__ void gauss3(const Stage3<real> &K, const real (&sm)[9][5], Left left, real (&Fs)[5], int &bad)
 {
-    const int m0 = S.n[0] + (A == 0), m1 = S.n[1] + (A == 1), m2 = S.n[2] + (A == 2);
-    const int nfa = m0 * m1 * m2;
-    const int loc = blockIdx.x * blockDim.x + threadIdx.x;
-    if (loc >= nfa) return;
-    const int i = loc % m0, rr = loc / m0, j = rr % m1, k = rr / m1;
-    const int lo[3] = {i - (A == 0), j - (A == 1), k - (A == 2)}, hi[3] = {i, j, k};
-    bool inside = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) inside = inside && lo[d] >= 2 && hi[d] + 2 < S.n[d];
-    real sl[9][5], sr[9][5];
-    if (inside) top2_states<A, true>(S, i, j, k, sl, sr);
-    else top2_states<A, false>(S, i, j, k, sl, sr);
-    const cptr<real> w = (cptr<real>)S.qw + 9;
-    real Fs[5] = {real(0), real(0), real(0), real(0), real(0)};
+    const cptr<real> w = (cptr<real>)K.qw + 9;
     bool bl = false, br = false;
 #pragma unroll
+    for (int v = 0; v < 5; ++v) Fs[v] = real(0);
+#pragma unroll
     for (int n = 0; n < 9; ++n) {
-        real fl[5];
+        real sl[5], fl[5];
+        left(n, sl);
         bool b1, b2;
-        hllc3(S.gamma, A, sl[n], sr[n], fl, b1, b2);
+        hllc3(K.gamma, A, sl, sm[n], fl, b1, b2);
         bl = bl || b1;
         br = br || b2;
 #pragma unroll
         for (int v = 0; v < 5; ++v) Fs[v] = fma(w[n], fl[v], Fs[v]);
+        hold(Fs);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    bad = (bl ? 1 : 0) | (br ? 2 : 0);
+}
+
+// One variable's states of a cell on its - face (sm) and + face (sp) of axis A.
+template <int A, typename real>
+__device__ __forceinline__ void sides3(const Stage3<real> &S, const real (&P)[kNPar3], int v, real (&sm)[9][5],
+                                       real (&sp)[9][5])
+{
+    const cptr<real> W = (cptr<real>)S.pz + 2 * A * 4 * kNPar3;
+    real st[9];
+    par3_states(P, W, st);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) S.F[A][(size_t)v * nfa + loc] = Fs[v];
-    S.Ff[A][loc] = (uint8_t)((bl ? 1 : 0) | (br ? 2 : 0));
+    for (int n = 0; n < 9; ++n) sm[n][v] = st[n];
+    par3_states(P, W + 4 * kNPar3, st);
+#pragma unroll
+    for (int n = 0; n < 9; ++n) sp[n][v] = st[n];
+}
+
+// First evaluation at radius 2 (k3_faces_x, k3_faces_march): a cell's ball is read once
+// for both of its faces on the axis, whose states share the parity entries, and a face
+// takes its left state from the cell one step back.  Bound by vector instructions (about
+// 2300 a cell in FP32) and, at three or four wavefronts a SIMD, the waits between them.
+// One thread per face that read both balls, with two wavefronts a SIMD in FP32 and one in
+// FP64, took 784, 780 and 705 us on x, y and z at 192^3 in FP32 and 163, 161 and 151 us at
+// 97 x 64 x 81 in FP64; now 337, 429 and 422 us, and 76, 108 and 107 us.  A tile of eight lanes
+// along y or z by eight columns, which needs no march, took 1000 us: a load of eight short
+// rows takes the cache twice as long as one of 64 cells in a row.
+//
+// On x the cell one step back is the previous lane's: a wavefront runs 64 positions of the
+// rows written one after the other, a ghost cell at either end included, and writes 63
+// faces.
+template <typename real, typename OFF>
+__global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k3_faces_x(const Stage3<real>)
+{
+    const Stage3<real> &S = first_arg<Stage3<real>>();
+    int pos[3], loc;
+    bool live;
+    {
+        const int len = S.n[0] + 2, total = len * S.n[1] * S.n[2], lane = threadIdx.x;
+        const int q = 63 * xcd_tile(blockIdx.x, gridDim.x) + lane, qc = min(q, total - 1), r = qc / len;
+        pos[0] = qc - r * len - 1;  // -1 and n: the ghost cells
+        pos[1] = r % S.n[1];
+        pos[2] = r / S.n[1];
+        live = lane > 0 && pos[0] >= 0 && q < total;
+        loc = r * (S.n[0] + 1) + pos[0];
+    }
+    OFF off[25];
+    {
+        const OFF row = (OFF)S.n[0] * (OFF)sizeof(real), stride[3] = {(OFF)sizeof(real), row, row * (OFF)S.n[1]};
+        OFF o[3][5];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int d = 0; d < 5; ++d) o[a][d] = (OFF)w3(pos[a] + d - 2, S.n[a], S.bc[a]) * stride[a];
+#pragma unroll
+        for (int m = 0; m < 25; ++m) off[m] = o[0][kBall[m][0] + 2] + o[1][kBall[m][1] + 2] + o[2][kBall[m][2] + 2];
+    }
+    auto fetch = [&](int v, real (&q)[25]) {
+        const Stage3<real> &K = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S);
+        const global_bytes U = (global_bytes)(K.Us + (size_t)v * K.n[0] * K.n[1] * K.n[2]);
+        ball3(off, q, [&](int) { return U; }, [](int m) { return m; });
+    };
+    real qn[25], sm[9][5], sp[9][5];
+    fetch(0, qn);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+        real P[kNPar3];
+        par3_entries<0>(qn, P);
+        hold(P);
+        if (v < 4) fetch(v + 1, qn);  // in flight during this variable's products
+        __builtin_amdgcn_sched_barrier(0);
+        sides3<0>(S, P, v, sm, sp);
+    }
+    const Stage3<real> &K = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S);
+    real Fs[5];
+    int bad;
+    gauss3<0>(
+        K, sm,
+        [&](int n, real (&sl)[5]) {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) sl[v] = lane_shift<-1>(sp[n][v]);
+        },
+        Fs, bad);
+    if (!live) return;
+    const size_t nfa = (size_t)(K.n[0] + 1) * K.n[1] * K.n[2];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) K.F[0][v * nfa + loc] = Fs[v];
+    K.Ff[0][loc] = (uint8_t)bad;
+}
+
+// On y and z a lane marches along the axis over `len` faces, the + states of the cell
+// before kept from one step to the next: in LDS, but for the last node's in FP64 (45
+// values a lane are 23 KB a wavefront, 40 are an eighth of a CU's LDS, which two
+// wavefronts on each SIMD take).  The 64 lanes are consecutive columns, x fastest, and
+// every load's offset along the axis is scalar.
+template <typename real, int A, typename OFF>
+__global__ __launch_bounds__(64, sizeof(real) == 4 ? 3 : 2) void k3_faces_march(const Stage3<real>, int len)
+{
+    constexpr int t2 = 3 - A;                        // the other axis of the columns
+    constexpr int kept = sizeof(real) == 4 ? 45 : 40;  // + states held in LDS
+    __shared__ real prev[kept][64];
+    const Stage3<real> &S = first_arg<Stage3<real>>();
+    const int lane = threadIdx.x;
+    int lo, hi, loc;
+    bool live;
+    OFF off[13];
+    {
+        const int cols = S.n[0] * S.n[t2], groups = (cols + 63) / 64;
+        const int wave = xcd_tile(blockIdx.x, gridDim.x), seg = wave / groups;
+        const int col = (wave - seg * groups) * 64 + lane, cc = min(col, cols - 1);
+        const int px = cc % S.n[0], pt = cc / S.n[0];
+        lo = seg * len;
+        hi = min(lo + len, S.n[A] + 1);
+        live = col < cols;
+        loc = (A == 1 ? pt * (S.n[1] + 1) : pt) * S.n[0] + px;  // face 0 of the column
+        const OFF row = (OFF)S.n[0] * (OFF)sizeof(real), stride = A == 1 ? row * (OFF)S.n[1] : row;
+        OFF ox[5], ot[5];
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            ox[d] = (OFF)w3(px + d - 2, S.n[0], S.bc[0]) * (OFF)sizeof(real);
+            ot[d] = (OFF)w3(pt + d - 2, S.n[t2], S.bc[t2]) * stride;
+        }
+#pragma unroll
+        for (int m = 0; m < 25; ++m) off[disc_index(kBall[m][0], kBall[m][t2])] = ox[kBall[m][0] + 2] + ot[kBall[m][t2] + 2];
+    }
+    // cell indices of the five positions along the axis about cell c (scalar)
+    int r[5];
+    auto rows = [&](int c) {
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            const int i = c + d - 2, n = S.n[A];
+            const int p = i < 0 ? i + n : (i >= n ? i - n : i), q = min(max(i, 0), n - 1);
+            r[d] = S.bc[A] == 0 ? p : q;
+        }
+    };
+    auto fetch = [&](int v, real (&q)[25]) {
+        const Stage3<real> &K = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S);
+        const size_t row = sizeof(real) * (size_t)K.n[0], slab = row * K.n[1];
+        const global_bytes U = (global_bytes)K.Us + v * slab * K.n[2];
+        global_bytes Ur[5];
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            Ur[d] = U + (size_t)r[d] * (A == 1 ? row : slab);
+            asm volatile("" : "+s"(Ur[d]));  // stays a scalar base
+        }
+        ball3(off, q, [&](int m) { return Ur[kBall[m][A] + 2]; },
+              [](int m) { return disc_index(kBall[m][0], kBall[m][t2]); });
+    };
+    real qn[25], last[5];
+    auto next = [&](int c) {
+        rows(min(c + 1, hi - 1));
+        fetch(0, qn);
+    };
+    rows(lo - 1);
+    fetch(0, qn);
+#pragma unroll 1
+    for (int c = lo - 1; c < hi; ++c) {
+        real sm[9][5], sp[9][5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            real P[kNPar3];
+            par3_entries<A>(qn, P);
+            hold(P);
+            // the next variable's loads are in flight during this one's products; the next
+            // cell's first in FP32 too (in FP64 the registers hold both sides' states then)
+            if (v < 4) fetch(v + 1, qn);
+            else if (kept == 45) next(c);
+            __builtin_amdgcn_sched_barrier(0);
+            sides3<A>(S, P, v, sm, sp);
+        }
+        auto keep = [&](int n) {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+                if (5 * n + v < kept) prev[5 * n + v][lane] = sp[n][v];
+                else last[v] = sp[n][v];
+            }
+        };
+        if (c < lo) {
+#pragma unroll
+            for (int n = 0; n < 9; ++n) keep(n);
+            if (kept != 45) next(c);
+            continue;
+        }
+        const Stage3<real> &K = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S);
+        real Fs[5];
+        int bad;
+        gauss3<A>(
+            K, sm,
+            [&](int n, real (&sl)[5]) {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) sl[v] = 5 * n + v < kept ? prev[5 * n + v][lane] : last[v];
+                keep(n);
+            },
+            Fs, bad);
+        if (kept != 45) next(c);
+        if (!live) continue;
+        const int k1 = K.n[1] + (A == 1);
+        const size_t nfa = (size_t)K.n[0] * k1 * (K.n[2] + (A == 2));
+        const size_t f = (size_t)loc + (size_t)c * (size_t)(A == 1 ? K.n[0] : K.n[0] * K.n[1]);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) K.F[A][v * nfa + f] = Fs[v];
+        K.Ff[A][f] = (uint8_t)bad;
+    }
+}
+
+// Faces per march of k3_faces_march on axis a: the longest of at most 6 that leaves three
+// marches for each of the 1024 SIMDs.  A march of T faces runs T + 1 cells, so a long one
+// runs fewer in all; but with fewer marches than that a SIMD waits on memory, and past 6
+// faces the last round of marches costs more than the extra cells.  Microseconds a step at
+// 1, 2, 3, 4, 6, 8, 12 faces: 32^3 FP64 275 334 377 432 547 666 890; 97 x 64 x 81 FP64
+// 1184 1075 1075 1101 1136 1294 1426; 64^3 FP32 418 414 423 473 527 609 731; 192^3 FP32
+// 5760 5000 4830 4700 4650 4730 4750, FP64 13510 11730 11300 11050 10850 10930 10940.
+static int march3(const int (&n)[3], int a, long long groups)
+{
+    int T = 6;
+    while (T > 1 && groups * ((n[a] + T) / T) < 3 * 1024) --T;
+    return T;
+}
+
+template <typename real, int A, typename OFF>
+static void launch_march(const Stage3<real> &S, hipStream_t st)
+{
+    const long long groups = ((long long)S.n[0] * S.n[3 - A] + 63) / 64;  // of 64 columns
+    const int len = march3(S.n, A, groups);
+    const dim3 g((unsigned)(groups * ((S.n[A] + len) / len)));
+    hipLaunchKernelGGL((k3_faces_march<real, A, OFF>), g, dim3(64), 0, st, S, len);
+}
+
+template <typename real, typename OFF>
+static void launch_top2(const Stage3<real> &S, hipStream_t st)
+{
+    const long long positions = (long long)(S.n[0] + 2) * S.n[1] * S.n[2];
+    hipLaunchKernelGGL((k3_faces_x<real, OFF>), dim3((unsigned)((positions + 61) / 63)), dim3(64), 0, st, S);
+    launch_march<real, 1, OFF>(S, st);
+    launch_march<real, 2, OFF>(S, st);
 }
 
 template <typename real, int R>
 static void launch_faces_top(const Stage3<real> &S, hipStream_t st)
 {
-    for (int a = 0; a < 3; ++a) {
-        const long long nfa = (long long)(S.n[0] + (a == 0)) * (S.n[1] + (a == 1)) * (S.n[2] + (a == 2));
-        const dim3 g((unsigned)((nfa + 127) / 128)), t(128);
-        if constexpr (R == 2) {
-            if (a == 0) hipLaunchKernelGGL((k3_faces_top2<real, 0>), g, t, 0, st, S);
-            if (a == 1) hipLaunchKernelGGL((k3_faces_top2<real, 1>), g, t, 0, st, S);
-            if (a == 2) hipLaunchKernelGGL((k3_faces_top2<real, 2>), g, t, 0, st, S);
-        } else {
+    if constexpr (R == 2) {
+        // byte offsets into a variable of 4 GiB or more take 64 bits
+        if ((unsigned long long)S.n[0] * S.n[1] * S.n[2] * sizeof(real) > 0xffffffffull) launch_top2<real, size_t>(S, st);
+        else launch_top2<real, unsigned>(S, st);
+    } else {
+        for (int a = 0; a < 3; ++a) {
+            const long long nfa = (long long)(S.n[0] + (a == 0)) * (S.n[1] + (a == 1)) * (S.n[2] + (a == 2));
+            const dim3 g((unsigned)((nfa + 127) / 128)), t(128);
             if (a == 0) hipLaunchKernelGGL((k3_faces_top<real, R, 0>), g, t, 0, st, S);
             if (a == 1) hipLaunchKernelGGL((k3_faces_top<real, R, 1>), g, t, 0, st, S);
             if (a == 2) hipLaunchKernelGGL((k3_faces_top<real, R, 2>), g, t, 0, st, S);

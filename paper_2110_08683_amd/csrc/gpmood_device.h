@@ -258,6 +258,15 @@ __device__ __forceinline__ cptr<T> reread(cptr<T> p)
     return p;
 }
 
+// The kernel's first argument where it lies in the kernel's argument block: read through
+// this reference a value is fetched again (a scalar load) rather than kept in a register
+// from the kernel's entry on.
+template <typename T>
+__device__ __forceinline__ const T &first_arg()
+{
+    return *(const T *)(cptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // The four parity sums of the mirror cells pp = (+a,+b), mp = (-a,+b),
 // pm = (+a,-b), mm = (-a,-b), paired along the diagonals so that exchanging the
 // axes (pm <-> mp) leaves EE and OO unchanged and swaps OE and EO bit for bit: a

@@ -29,15 +29,6 @@
 
 namespace gpm {
 
-// The kernel's first argument where it lies in the kernel's argument block: read through
-// this reference a value is fetched again (a scalar load) rather than kept in a register
-// from the kernel's entry on.
-template <typename T>
-__device__ __forceinline__ const T &first_arg()
-{
-    return *(const T *)(cptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
-}
-
 constexpr int LW = 70;  // LDS columns per ring row: 64 lanes + 3 halo columns each side
 
 // One wavefront's strip (tile wid of the problem) of the first pass; ring is the
