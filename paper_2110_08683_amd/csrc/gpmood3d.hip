@@ -224,13 +224,12 @@ __device__ __forceinline__ void face3_flux(const Stage3<real> &S, int f)
 }
 
 template <typename real>
-__global__ __launch_bounds__(128) void k3_faces(const Stage3<real> S, const int *list, const int *count, int all)
+__global__ __launch_bounds__(128) void k3_faces(const Stage3<real> S, const int *list, const int *count)
 {
     const int cap = S.fofs[3];
-    int n = all ? cap : *count;
+    int n = *count;
     n = n < cap ? n : cap;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-        face3_flux(S, all ? t : list[t]);
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) face3_flux(S, list[t]);
 }
 
 // First evaluation: every face of axis A at the top radius R (every cell starts the
@@ -764,24 +763,22 @@ __device__ __forceinline__ void claims3(const Stage3<real> &S, const PassOut3 &P
 }
 
 template <typename real>
-__device__ __forceinline__ bool troubled3(const Stage3<real> &S, int o, const real (&ust)[5], bool rs, int i, int j,
-                                          int k)
+__device__ __forceinline__ bool troubled3(const Stage3<real> &S0, int o, const real (&ust)[5], bool rs,
+                                          const real (&r7)[7], int i, int j, int k)
 {
     if (o == 0) return false;
+    const Stage3<real> &S = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S0);
     const size_t plane = (size_t)S.n[0] * S.n[1] * S.n[2];
     const real g = S.gamma;
     const real rho = ust[0], p = p3(g, ust);
     if (!(finite(rho) && finite(p))) return true;
     if ((S.flags & 8u) && rs) return true;
     if (!(rho > real(0) && p > real(0))) return true;
-    real r25[25];
-#pragma unroll
-    for (int m = 0; m < 25; ++m) r25[m] = S.Us[cell3(S, i + kBall[m][0], j + kBall[m][1], k + kBall[m][2])];
-    real lo = r25[0], hi = r25[0];
+    real lo = r7[0], hi = r7[0];
 #pragma unroll
     for (int m = 1; m < 7; ++m) {
-        lo = vmin(lo, r25[m]);
-        hi = vmax(hi, r25[m]);
+        lo = vmin(lo, r7[m]);
+        hi = vmax(hi, r7[m]);
     }
     if (lo <= rho && rho <= hi) return false;                   // DMP
     if ((S.flags & 2u) && (hi - lo) < S.plat_thr) return false;  // plateau
@@ -804,6 +801,10 @@ __device__ __forceinline__ bool troubled3(const Stage3<real> &S, int o, const re
         if (divV >= -S.sigma_v && gradp <= S.sigma_p) return false;
     }
     if (S.flags & 4u) {  // u2
+        real r25[25];
+#pragma unroll
+        for (int m = 0; m < 25; ++m)
+            r25[m] = m < 7 ? r7[m] : S.Us[cell3(S, i + kBall[m][0], j + kBall[m][1], k + kBall[m][2])];
         // index in kBall of the offset (di, dj, dk) with |di|+|dj|+|dk| <= 2
         auto at = [&](int di, int dj, int dk) {
             int r = 0;
@@ -846,75 +847,87 @@ __device__ __forceinline__ bool troubled3(const Stage3<real> &S, int o, const re
     return true;
 }
 
-template <typename real>
-__global__ __launch_bounds__(128) void k3_cells(const Stage3<real> S, const int *list, const int *count, int all,
-                                                PassOut3 P)
+// ALL: the first evaluation, every cell at the top radius.  Bound by memory: each flux is
+// read by the two cells of its face, so blocks go in runs to the XCDs, whose L2 then serves
+// the second.  The arguments are read again where they are used (held from the kernel's
+// entry they were moved to and from vector lanes, 600 instructions), the 18 outer cells of
+// the density ball only where u2 is reached, and the claims run only in a wavefront with a
+// lowered cell.  Measured: 192^3 FP32 322 -> 175 us (870 MB at least, 5.0 TB/s), 97 x 64 x
+// 81 FP64 47 -> 30 us.
+template <typename real, bool ALL>
+__global__ __launch_bounds__(128) void k3_cells(const Stage3<real>, const int *list, const int *count, PassOut3 P)
 {
+    const Stage3<real> &S = first_arg<Stage3<real>>();
+    auto again = [&]() -> const Stage3<real> & { return *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S); };
     const int nc = S.n[0] * S.n[1] * S.n[2];
-    int n = all ? nc : *count;
+    int n = ALL ? nc : *count;
     n = n < nc ? n : nc;
-    if (n <= (int)(blockIdx.x * blockDim.x)) return;
+    const int block = ALL ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    if (n <= block * (int)blockDim.x) return;
     P.stamp = *S.stamp0 + P.stamp;  // P.stamp carries the pass index
     const size_t plane = (size_t)nc;
     const real dt = (real)(*S.dt);
     const int stride = gridDim.x * blockDim.x;
     const int nround = (n + stride - 1) / stride;
     for (int r = 0; r < nround; ++r) {
-        const int idx = r * stride + blockIdx.x * blockDim.x + threadIdx.x;
+        const int idx = r * stride + block * blockDim.x + threadIdx.x;
         bool tr = false;
         int i = 0, j = 0, k = 0;
         if (idx < n) {
-            const int c = all ? idx : list[idx];
-            i = c % S.n[0];
-            j = (c / S.n[0]) % S.n[1];
-            k = c / (S.n[0] * S.n[1]);
+            const int c = ALL ? idx : list[idx];
+            const Stage3<real> &G = again();
+            i = c % G.n[0];
+            const int jk = c / G.n[0];
+            j = jk % G.n[1];
+            k = jk / G.n[1];
             real ust[5];
             real div[5] = {real(0), real(0), real(0), real(0), real(0)};
             // every flux, flag and state value of the cell loaded first, then one
             // wait (the flag tests and the divisions had split the loads by axis)
-            real fpv[3][5], fmv[3][5], us[5];
+            real fpv[3][5], fmv[3][5], us[5], r7[7];
             int fl = 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const int m0 = S.n[0] + (a == 0), m1 = S.n[1] + (a == 1), m2 = S.n[2] + (a == 2);
+                const Stage3<real> &H = again();
+                const int m0 = H.n[0] + (a == 0), m1 = H.n[1] + (a == 1), m2 = H.n[2] + (a == 2);
                 const size_t nfa = (size_t)m0 * m1 * m2;
                 const int fm = (k * m1 + j) * m0 + i;
                 const int fp = ((k + (a == 2)) * m1 + j + (a == 1)) * m0 + i + (a == 0);
 #pragma unroll
                 for (int v = 0; v < 5; ++v) {
-                    fpv[a][v] = S.F[a][v * nfa + fp];
-                    fmv[a][v] = S.F[a][v * nfa + fm];
+                    fpv[a][v] = H.F[a][v * nfa + fp];
+                    fmv[a][v] = H.F[a][v * nfa + fm];
                 }
-                fl |= S.Ff[a][fm] | S.Ff[a][fp];  // either side of either face
+                fl |= H.Ff[a][fm] | H.Ff[a][fp];  // either side of either face
             }
+            const Stage3<real> &V = again();
 #pragma unroll
-            for (int v = 0; v < 5; ++v) us[v] = S.Us[v * plane + c];
-            const int o = S.order[c];
+            for (int v = 0; v < 5; ++v) us[v] = V.Us[v * plane + c];
+            r7[0] = us[0];
+#pragma unroll
+            for (int m = 1; m < 7; ++m) r7[m] = V.Us[cell3(V, i + kBall[m][0], j + kBall[m][1], k + kBall[m][2])];
+            const int o = ALL ? V.top : V.order[c];
             __builtin_amdgcn_sched_barrier(0);
             const bool rs = fl != 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int v = 0; v < 5; ++v) div[v] = div[v] + (fpv[a][v] - fmv[a][v]) / S.d[a];
+                for (int v = 0; v < 5; ++v) div[v] = div[v] + (fpv[a][v] - fmv[a][v]) / V.d[a];
 #pragma unroll
             for (int v = 0; v < 5; ++v) ust[v] = us[v] - dt * div[v];
-            tr = troubled3(S, o, ust, rs, i, j, k);
+            tr = troubled3(S, o, ust, rs, r7, i, j, k);
+            const Stage3<real> &W = again();
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
-                const real un = S.s == 0 ? real(0) : S.Un[v * plane + c];
-                S.Uout[v * plane + c] = combine(S.s, un, ust[v]);
+                const real un = W.s == 0 ? real(0) : W.Un[v * plane + c];
+                W.Uout[v * plane + c] = combine(W.s, un, ust[v]);
             }
-            if (tr) S.order[c] = (uint8_t)next_radius(S.next[0], S.next[1], S.next[2], S.next[3], o);
+            if (ALL || tr)
+                W.order[c] = (uint8_t)(tr ? next_radius(W.next[0], W.next[1], W.next[2], W.next[3], o) : o);
         }
         wave_count(tr, P.tcount);
-        claims3(S, P, i, j, k, tr);
+        if (__ballot(tr) != 0ull) claims3(again(), P, i, j, k, tr);
     }
-}
-
-__global__ void k3_fill_order(uint8_t *order, size_t n, int top)
-{
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
-        order[t] = (uint8_t)top;
 }
 
 __global__ void k3_reset(Ctl *ctl, int nzero, unsigned stamp0)
@@ -1153,15 +1166,11 @@ static gpm_status stage3(gpm3_ctx *c, int s, const void *Un, const void *Us, voi
     const int nzero = c->fresh ? kMaxPasses + 2 : (c->last_npass + 3 < kMaxPasses + 2 ? c->last_npass + 3 : kMaxPasses + 2);
     c->fresh = false;
     hipLaunchKernelGGL(k3_reset, dim3(1), dim3(256), 0, c->stream, c->ctl, nzero, stamp0);
-    hipLaunchKernelGGL(k3_fill_order, dim3(1024), dim3(256), 0, c->stream, c->order, c->ncell, c->top);
     // first evaluation: every face at the top radius, then every cell
-    int nbf = (int)((c->nfaces + 127) / 128);
-    if (nbf > 65536) nbf = 65536;
     int nbc = (int)((c->ncell + 127) / 128);
     if (nbc > 65536) nbc = 65536;
     if (c->top == 2) launch_faces_top<real, 2>(S, c->stream);
-    else if (c->top == 1) launch_faces_top<real, 1>(S, c->stream);
-    else hipLaunchKernelGGL(k3_faces<real>, dim3(nbf), dim3(128), 0, c->stream, S, (const int *)nullptr, (const int *)nullptr, 1);
+    else launch_faces_top<real, 1>(S, c->stream);  // a scheme's top radius is 1 or 2
     PassOut3 P;
     P.flist = c->flist[1];
     P.clist = c->clist[1];
@@ -1169,7 +1178,7 @@ static gpm_status stage3(gpm3_ctx *c, int s, const void *Un, const void *Us, voi
     P.ccount = &c->ctl->ncell[1];
     P.tcount = &c->ctl->ntroub[0];
     P.stamp = 0;
-    hipLaunchKernelGGL(k3_cells<real>, dim3(nbc), dim3(128), 0, c->stream, S, (const int *)nullptr, (const int *)nullptr, 1, P);
+    hipLaunchKernelGGL((k3_cells<real, true>), dim3(nbc), dim3(128), 0, c->stream, S, (const int *)nullptr, (const int *)nullptr, P);
     H3(c, hipGetLastError());
     // cascade passes in batches, with a host check of the counts per batch
     int nb = (int)((c->ncell + 127) / 128);
@@ -1184,7 +1193,7 @@ static gpm_status stage3(gpm3_ctx *c, int s, const void *Un, const void *Us, voi
             return f3(c, GPM_ENOTCONV, "MOOD loop exceeded the pass limit");
         }
         for (int b = 0; b < batch; ++b, ++k) {
-            hipLaunchKernelGGL(k3_faces<real>, dim3(nb), dim3(128), 0, c->stream, S, c->flist[k & 1], &c->ctl->nface[k], 0);
+            hipLaunchKernelGGL(k3_faces<real>, dim3(nb), dim3(128), 0, c->stream, S, c->flist[k & 1], &c->ctl->nface[k]);
             PassOut3 Q;
             Q.flist = c->flist[(k + 1) & 1];
             Q.clist = c->clist[(k + 1) & 1];
@@ -1192,7 +1201,7 @@ static gpm_status stage3(gpm3_ctx *c, int s, const void *Un, const void *Us, voi
             Q.ccount = &c->ctl->ncell[k + 1];
             Q.tcount = &c->ctl->ntroub[k];
             Q.stamp = (unsigned)k;
-            hipLaunchKernelGGL(k3_cells<real>, dim3(nb), dim3(128), 0, c->stream, S, c->clist[k & 1], &c->ctl->ncell[k], 0, Q);
+            hipLaunchKernelGGL((k3_cells<real, false>), dim3(nb), dim3(128), 0, c->stream, S, c->clist[k & 1], &c->ctl->ncell[k], Q);
         }
         H3(c, hipGetLastError());
         if (batch < 32) batch *= 2;
