@@ -335,15 +335,6 @@ __device__ __forceinline__ void par3_entries(const real (&q)[25], real (&P)[kNPa
     }
 }
 
-// Keeps values where they are computed: without it instruction selection moves the
-// products past the next group's weight loads.
-template <int N, typename real>
-__device__ __forceinline__ void hold(real (&x)[N])
-{
-#pragma unroll
-    for (int m = 0; m < N; ++m) asm volatile("" : "+v"(x[m]));
-}
-
 // Sum of the entries E0..E1-1 with weights w[0..]; the products in order of the entry.
 template <int E0, int E1, typename real>
 __device__ __forceinline__ real par3_dot(const real *w, const real (&P)[kNPar3])

@@ -575,10 +575,7 @@ static gpm_status stage_vjp(gpm_ctx *c, const Weights<real> &W, int s, const voi
     hipError_t e = launch_set_dt(c->ctl, dt, c->stream);
     if (e != hipSuccess) return fail(c, GPM_EHIP, hipGetErrorString(e));
     J.A.dt = &c->ctl->dt;
-    const size_t nft = nfaces_x(c) + nfaces_y(c);
-    int nblk = (int)((nft + 127) / 128);
-    if (nblk > kTotBlocks * 8) nblk = kTotBlocks * 8;
-    e = launch_stage_vjp<real>(J, nblk, dl_dev ? dl_dev : &c->ctl->totals[0], dl_dev != nullptr, c->stream);
+    e = launch_stage_vjp<real>(J, dl_dev ? dl_dev : &c->ctl->totals[0], dl_dev != nullptr, c->stream);
     if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("stage adjoint: ") + hipGetErrorString(e));
     if (dL_dell) {
         double d = 0.0;

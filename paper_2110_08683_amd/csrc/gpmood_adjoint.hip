@@ -196,184 +196,279 @@ struct alignas(16) Quad {
 };
 
 // ------------------------------------------------------------ per-face adjoint
-template <typename real>
-__global__ __launch_bounds__(128) void k_adj_faces(const AdjArgs<real> J)
+// The four corner values of stencil position E of both sides' cells, variable by
+// variable: u[v][0..3] the left side's (++, -+, +-, --), u[v][4..7] the right's.  xo, yo:
+// byte offsets of the columns iL - 3.. and the rows jL - 3..
+template <int DIR, int E, typename real>
+__device__ __forceinline__ void top_corners(const StageArgs<real> &A, const unsigned (&xo)[8], const unsigned (&yo)[8],
+                                            real (&u)[4][8])
+{
+    constexpr int a = (int)((kPosA >> (4 * E)) & 15u), b = (int)((kPosB >> (4 * E)) & 15u);
+    const StageArgs<real> &K = *(const StageArgs<real> *)reread((cptr<StageArgs<real>>)&A);
+    const size_t plane = (size_t)K.nx * K.ny;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int cx = 3 + (DIR == 0 ? s : 0), cy = 3 + (DIR == 1 ? s : 0);
+        const unsigned o[4] = {yo[cy + b] + xo[cx + a], yo[cy + b] + xo[cx - a], yo[cy - b] + xo[cx + a], yo[cy - b] + xo[cx - a]};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const char *U = (const char *)(K.Us + v * plane);
+            u[v][4 * s] = *(const real *)(U + o[0]);
+            u[v][4 * s + 1] = a == 0 ? u[v][4 * s] : *(const real *)(U + o[1]);
+            u[v][4 * s + 2] = b == 0 ? u[v][4 * s] : *(const real *)(U + o[2]);
+            u[v][4 * s + 3] = b == 0 ? u[v][4 * s + 1] : (a == 0 ? u[v][4 * s + 2] : *(const real *)(U + o[3]));
+        }
+    }
+}
+
+// The accumulators of both sides of a face at the top radius 3, position by position in
+// the order of the general path; the next position's loads are in flight during one's
+// products, and its 8 weights are read through the scalar path.
+template <int DIR, int E, typename real>
+__device__ __forceinline__ void top_accumulators(const StageArgs<real> &A, const unsigned (&xo)[8], const unsigned (&yo)[8],
+                                                 real (&u)[4][8], real (&PL)[4][2][4], real (&PR)[4][2][4])
+{
+    if constexpr (E < kNPos) {
+        real un[4][8];
+        if constexpr (E + 1 < kNPos) top_corners<DIR, E + 1>(A, xo, yo, un);
+        const StageArgs<real> &K = *(const StageArgs<real> *)reread((cptr<StageArgs<real>>)&A);
+        const cptr<real> wt = (cptr<real>)K.gtab + (3 * 2 + DIR) * kGtabPerDir;
+        real w[2][4];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[p][c] = wt[p * (kNPos * 4) + E * 4 + c];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            real ql[4], qr[4];
+            parity4(u[v][0], u[v][1], u[v][2], u[v][3], ql);
+            parity4(u[v][4], u[v][5], u[v][6], u[v][7], qr);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    PL[v][p][c] = fma(w[p][c], ql[c], PL[v][p][c]);
+                    PR[v][p][c] = fma(w[p][c], qr[c], PR[v][p][c]);
+                }
+                hold(PL[v][p]);
+                hold(PR[v][p]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        top_accumulators<DIR, E + 1>(A, xo, yo, un, PL, PR);
+    }
+}
+
+// Accumulators of both sides of a face of radius R, lane by lane.
+template <int DIR, typename real>
+__device__ __forceinline__ void any_accumulators(const StageArgs<real> &A, int R, int iL, int jL, real (&PL)[4][2][4],
+                                                 real (&PR)[4][2][4])
+{
+    const int nx = A.nx, ny = A.ny, iR = iL + (DIR == 0), jR = jL + (DIR == 1);
+    const size_t plane = (size_t)nx * ny;
+    const int np = R <= 0 ? 1 : (R == 1 ? 3 : (R == 2 ? 6 : 10));
+    const real *wt = A.gtab + (R * 2 + DIR) * kGtabPerDir;
+    for (int e = 0; e < np; ++e) {
+        const int a = (int)((kPosA >> (4 * e)) & 15u), b = (int)((kPosB >> (4 * e)) & 15u);
+        const int xLp = wrap(iL + a, nx, A.bcx), xLm = wrap(iL - a, nx, A.bcx);
+        const int xRp = wrap(iR + a, nx, A.bcx), xRm = wrap(iR - a, nx, A.bcx);
+        const size_t yLp = (size_t)wrap(jL + b, ny, A.bcy) * nx, yLm = (size_t)wrap(jL - b, ny, A.bcy) * nx;
+        const size_t yRp = (size_t)wrap(jR + b, ny, A.bcy) * nx, yRm = (size_t)wrap(jR - b, ny, A.bcy) * nx;
+        // the position's 32 values and 8 weights, all loads issued before the
+        // arithmetic that waits for them
+        real u[4][8], wq[2][4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const real *U = A.Us + v * plane;
+            u[v][0] = U[yLp + xLp];
+            u[v][1] = U[yLp + xLm];
+            u[v][2] = U[yLm + xLp];
+            u[v][3] = U[yLm + xLm];
+            u[v][4] = U[yRp + xRp];
+            u[v][5] = U[yRp + xRm];
+            u[v][6] = U[yRm + xRp];
+            u[v][7] = U[yRm + xRm];
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) wq[p][c] = wt[p * (kNPos * 4) + e * 4 + c];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            real ql[4], qr[4];
+            parity4(u[v][0], u[v][1], u[v][2], u[v][3], ql);
+            parity4(u[v][4], u[v][5], u[v][6], u[v][7], qr);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    PL[v][p][c] = fma(wq[p][c], ql[c], PL[v][p][c]);
+                    PR[v][p][c] = fma(wq[p][c], qr[c], PR[v][p][c]);
+                }
+        }
+    }
+}
+
+// One node's states, J^T (w_g lambda_F) and its share of the accumulators' adjoints.
+template <int DIR, typename real>
+__device__ __forceinline__ void node_adj(real gamma, real wq, const real (&lF)[4], int slot, bool single, bool plus,
+                                         const real (&PL)[4][2][4], const real (&PR)[4][2][4], real (&gL)[4][2][4],
+                                         real (&gR)[4][2][4])
+{
+    constexpr int OF = DIR ? C_EO : C_OE, ON = DIR ? C_OE : C_EO;  // odd across / along the face
+    const real sg = single ? real(0) : (plus ? real(1) : real(-1));
+    real UL[4], UR[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        real l[4], r[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            l[c] = slot ? PL[v][1][c] : PL[v][0][c];
+            r[c] = slot ? PR[v][1][c] : PR[v][0][c];
+        }
+        const real Ap = l[C_EE] + l[OF], Cp = l[ON] + l[C_OO];
+        const real Bm = r[C_EE] - r[OF], Dm = r[ON] - r[C_OO];
+        UL[v] = single ? Ap : (plus ? Ap + Cp : Ap - Cp);
+        UR[v] = single ? Bm : (plus ? Bm + Dm : Bm - Dm);
+    }
+    // d(w_g lambda_F . F) / d(UL, UR), momenta rotated into the x-face form
+    constexpr int n = 1 + DIR, t = 2 - DIR;
+    const real wx[4] = {wq * lF[0], wq * lF[n], wq * lF[t], wq * lF[3]};
+    const real L4[4] = {UL[0], UL[n], UL[t], UL[3]};
+    const real R4[4] = {UR[0], UR[n], UR[t], UR[3]};
+    real gxl[4], gxr[4];
+    hllc_vjp(gamma, L4, R4, wx, gxl, gxr);
+    const real gs[8] = {gxl[0], gxl[n], gxl[t], gxl[3], gxr[0], gxr[n], gxr[t], gxr[3]};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        // left state A + sg C with A = EE + F, C = N + OO; right state
+        // Bm + sg D with Bm = EE - F, D = N - OO (F, N: OE / EO by direction)
+        const real la = gs[v], lc = sg * gs[v], rb = gs[4 + v], rd = sg * gs[4 + v];
+        const real cl[4] = {la, DIR ? lc : la, DIR ? la : lc, lc};
+        const real cr[4] = {rb, DIR ? rd : -rb, DIR ? -rb : rd, -rd};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            gL[v][0][c] += slot == 0 ? cl[c] : real(0);
+            gL[v][1][c] += slot == 1 ? cl[c] : real(0);
+            gR[v][0][c] += slot == 0 ? cr[c] : real(0);
+            gR[v][1][c] += slot == 1 ? cr[c] : real(0);
+        }
+    }
+}
+
+// Face f of direction DIR.
+template <int DIR, typename real>
+__device__ __forceinline__ void face_adj(const AdjArgs<real> &J, int f)
 {
     const StageArgs<real> &A = J.A;
     const int nx = A.nx, ny = A.ny;
     const size_t plane = (size_t)nx * ny;
     // a periodic axis has one face per cell along it (the face at the wrap joins
     // cells n-1 and 0), an outflow axis n + 1
-    const int fxn = A.bcx == 0 ? nx : nx + 1, fyn = A.bcy == 0 ? ny : ny + 1;
-    const int nfx = fxn * ny, nft = nfx + nx * fyn;
+    const int row = DIR == 0 && A.bcx != 0 ? nx + 1 : nx;
+    const int rows = DIR == 1 && A.bcy != 0 ? ny + 1 : ny;
+    if (f >= row * rows) return;
+    const int j = f / row, i = f - j * row;  // between cells i-1 and i, or j-1 and j
+    const int iL = i - (DIR == 0), jL = j - (DIR == 1);
+    const bool hasL = DIR == 0 ? A.bcx == 0 || i >= 1 : A.bcy == 0 || j >= 1;
+    const bool hasR = DIR == 0 ? A.bcx == 0 || i < nx : A.bcy == 0 || j < ny;
+    const int cL = wrap(jL, ny, A.bcy) * nx + wrap(iL, nx, A.bcx);
+    const int cR = wrap(j, ny, A.bcy) * nx + wrap(i, nx, A.bcx);
     const real alpha = A.s == 0 ? real(1) : (A.s == 1 ? real(0.25) : real(2) / real(3));
     const real dt = (real)(*A.dt);
-    for (int f = blockIdx.x * blockDim.x + threadIdx.x; f < nft; f += gridDim.x * blockDim.x) {
-        int dir, iL, jL, i, j;
-        bool hasL, hasR;
-        if (f < nfx) {
-            dir = 0;
-            j = f / fxn;
-            i = f - j * fxn;  // between cells i-1 and i
-            iL = i - 1;
-            jL = j;
-            hasL = A.bcx == 0 || i >= 1;
-            hasR = A.bcx == 0 || i < nx;
-        } else {
-            dir = 1;
-            const int g = f - nfx;
-            j = g / nx;
-            i = g - j * nx;  // between cells (i, j-1) and (i, j)
-            iL = i;
-            jL = j - 1;
-            hasL = A.bcy == 0 || j >= 1;
-            hasR = A.bcy == 0 || j < ny;
-        }
-        const int iR = iL + (dir == 0), jR = jL + (dir == 1);
-        const int cL = wrap(jL, ny, A.bcy) * nx + wrap(iL, nx, A.bcx);
-        const int cR = wrap(jR, ny, A.bcy) * nx + wrap(iR, nx, A.bcx);
-        const real inv = dt / (dir == 0 ? A.dx : A.dy);
-        real lF[4];
-        bool any = false;
+    const real inv = dt / (DIR == 0 ? A.dx : A.dy);
+    const int R = min((int)A.order[cL], (int)A.order[cR]);
+    real lF[4];
+    bool any = false;
 #pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const real lr = hasR ? J.lam_out[v * plane + cR] : real(0);
+        const real ll = hasL ? J.lam_out[v * plane + cL] : real(0);
+        lF[v] = (alpha * lr - alpha * ll) * inv;
+        any = any || lF[v] != real(0);
+    }
+    if (!any) {
+        // nothing flows through this face: its record holds zeros
+        const Quad<real> z = {{real(0), real(0), real(0), real(0)}};
         for (int v = 0; v < 4; ++v) {
-            const real lr = hasR ? J.lam_out[v * plane + cR] : real(0);
-            const real ll = hasL ? J.lam_out[v * plane + cL] : real(0);
-            lF[v] = (alpha * lr - alpha * ll) * inv;
-            any = any || lF[v] != real(0);
+            Quad<real> *blk = reinterpret_cast<Quad<real> *>(record_block(J, DIR, v, i, j));
+#pragma unroll
+            for (int k4 = 0; k4 < 4; ++k4) blk[k4] = z;
         }
-        if (!any) {
-            // nothing flows through this face: its record holds zeros
-            const Quad<real> z = {{real(0), real(0), real(0), real(0)}};
-            for (int v = 0; v < 4; ++v) {
-                Quad<real> *blk = reinterpret_cast<Quad<real> *>(record_block(J, dir, v, i, j));
+        return;
+    }
+    real PL[4][2][4], PR[4][2][4], gL[4][2][4], gR[4][2][4];
 #pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) blk[k4] = z;
-            }
-            continue;
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) PL[v][p][c] = PR[v][p][c] = gL[v][p][c] = gR[v][p][c] = real(0);
+    // 1. accumulators of both cells (quarter basis, as the forward); 2-3. per node:
+    // states, J^T (w_g lambda_F), adjoints of the accumulators.  A wavefront whose faces
+    // all have radius 3 takes the first form (where 32-bit byte offsets reach a variable's
+    // end): compile-time positions, whose coinciding corners are read once, and nodes.
+    if (__all(R == 3) && plane * sizeof(real) <= 0xffffffffull) {
+        unsigned xo[8], yo[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            xo[d] = (unsigned)wrap(iL + d - 3, nx, A.bcx) * (unsigned)sizeof(real);
+            yo[d] = (unsigned)wrap(jL + d - 3, ny, A.bcy) * (unsigned)nx * (unsigned)sizeof(real);
         }
-        const int R = min((int)A.order[cL], (int)A.order[cR]);
-        const int np = R <= 0 ? 1 : (R == 1 ? 3 : (R == 2 ? 6 : 10));
-        const int q = R <= 0 ? 1 : R + 1;
-        const real *wt = A.gtab + (R * 2 + dir) * kGtabPerDir;
-        // 1. accumulators of both cells (quarter basis, as the forward)
-        real PL[4][2][4], PR[4][2][4];
+        real u[4][8];
+        top_corners<DIR, 0>(A, xo, yo, u);
+        top_accumulators<DIR, 0>(A, xo, yo, u, PL, PR);
+        const StageArgs<real> &K = *(const StageArgs<real> *)reread((cptr<StageArgs<real>>)&A);
+        const cptr<real> wn = (cptr<real>)K.gtab + kGtabNodeOff + 3 * 2;
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) PL[v][p][c] = PR[v][p][c] = real(0);
-        for (int e = 0; e < np; ++e) {
-            const int a = (int)((kPosA >> (4 * e)) & 15u), b = (int)((kPosB >> (4 * e)) & 15u);
-            const int xLp = wrap(iL + a, nx, A.bcx), xLm = wrap(iL - a, nx, A.bcx);
-            const int xRp = wrap(iR + a, nx, A.bcx), xRm = wrap(iR - a, nx, A.bcx);
-            const size_t yLp = (size_t)wrap(jL + b, ny, A.bcy) * nx, yLm = (size_t)wrap(jL - b, ny, A.bcy) * nx;
-            const size_t yRp = (size_t)wrap(jR + b, ny, A.bcy) * nx, yRm = (size_t)wrap(jR - b, ny, A.bcy) * nx;
-            // the position's 32 values and 8 weights, all loads issued before the
-            // arithmetic that waits for them
-            real u[4][8], wq[2][4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const real *U = A.Us + v * plane;
-                u[v][0] = U[yLp + xLp];
-                u[v][1] = U[yLp + xLm];
-                u[v][2] = U[yLm + xLp];
-                u[v][3] = U[yLm + xLm];
-                u[v][4] = U[yRp + xRp];
-                u[v][5] = U[yRp + xRm];
-                u[v][6] = U[yRm + xRp];
-                u[v][7] = U[yRm + xRm];
-            }
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) wq[p][c] = wt[p * (kNPos * 4) + e * 4 + c];
+        for (int k = 0; k < 4; ++k) {
+            const int slot = k == 1 || k == 2 ? 1 : 0;
+            node_adj<DIR>(K.gamma, wn[slot], lF, slot, false, k < 2, PL, PR, gL, gR);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                real ql[4], qr[4];
-                parity4(u[v][0], u[v][1], u[v][2], u[v][3], ql);
-                parity4(u[v][4], u[v][5], u[v][6], u[v][7], qr);
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        PL[v][p][c] = fma(wq[p][c], ql[c], PL[v][p][c]);
-                        PR[v][p][c] = fma(wq[p][c], qr[c], PR[v][p][c]);
-                    }
-            }
         }
-        // 2-3. per node: states, J^T (w_g lambda_F), adjoints of the accumulators
-        real gL[4][2][4], gR[4][2][4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) gL[v][p][c] = gR[v][p][c] = real(0);
+    } else {
+        any_accumulators<DIR>(A, R, iL, jL, PL, PR);
+        const int q = R <= 0 ? 1 : R + 1;
         for (int k = 0; k < q; ++k) {
             const int slot = (R >= 2 && k >= 1 && k <= q - 2) ? 1 : 0;
-            const bool single = R <= 0 || (R == 2 && k == 1);
-            const bool plus = k < (q >> 1);
-            const real sg = single ? real(0) : (plus ? real(1) : real(-1));
-            real UL[4], UR[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const real lee = slot ? PL[v][1][C_EE] : PL[v][0][C_EE], loe = slot ? PL[v][1][C_OE] : PL[v][0][C_OE];
-                const real leo = slot ? PL[v][1][C_EO] : PL[v][0][C_EO], loo = slot ? PL[v][1][C_OO] : PL[v][0][C_OO];
-                const real ree = slot ? PR[v][1][C_EE] : PR[v][0][C_EE], roe = slot ? PR[v][1][C_OE] : PR[v][0][C_OE];
-                const real reo = slot ? PR[v][1][C_EO] : PR[v][0][C_EO], roo = slot ? PR[v][1][C_OO] : PR[v][0][C_OO];
-                const real lF = dir ? leo : loe, lN = dir ? loe : leo;  // odd across / along the face
-                const real rF = dir ? reo : roe, rN = dir ? roe : reo;
-                const real Ap = lee + lF, Cp = lN + loo;
-                const real Bm = ree - rF, Dm = rN - roo;
-                UL[v] = single ? Ap : (plus ? Ap + Cp : Ap - Cp);
-                UR[v] = single ? Bm : (plus ? Bm + Dm : Bm - Dm);
-            }
-            const real wq_ = A.gtab[kGtabNodeOff + R * 2 + slot];
-            // d(w_g lambda_F . F) / d(UL, UR), momenta rotated into the x-face form
-            const real wx[4] = {wq_ * lF[0], wq_ * (dir ? lF[2] : lF[1]), wq_ * (dir ? lF[1] : lF[2]), wq_ * lF[3]};
-            const real L4[4] = {UL[0], dir ? UL[2] : UL[1], dir ? UL[1] : UL[2], UL[3]};
-            const real R4[4] = {UR[0], dir ? UR[2] : UR[1], dir ? UR[1] : UR[2], UR[3]};
-            real gxl[4], gxr[4];
-            hllc_vjp(A.gamma, L4, R4, wx, gxl, gxr);
-            const real gs[8] = {gxl[0], dir ? gxl[2] : gxl[1], dir ? gxl[1] : gxl[2], gxl[3],
-                                gxr[0], dir ? gxr[2] : gxr[1], dir ? gxr[1] : gxr[2], gxr[3]};
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                // left state A + sg C with A = EE + F, C = N + OO; right state
-                // Bm + sg D with Bm = EE - F, D = N - OO (F, N: OE / EO by direction)
-                const real la = gs[v], lc = sg * gs[v], rb = gs[4 + v], rd = sg * gs[4 + v];
-                const real cl[4] = {la, dir ? lc : la, dir ? la : lc, lc};
-                const real cr[4] = {rb, dir ? rd : -rb, dir ? -rb : rd, -rd};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    gL[v][0][c] += slot == 0 ? cl[c] : real(0);
-                    gL[v][1][c] += slot == 1 ? cl[c] : real(0);
-                    gR[v][0][c] += slot == 0 ? cr[c] : real(0);
-                    gR[v][1][c] += slot == 1 ? cr[c] : real(0);
-                }
-            }
-        }
-        // 4. the face's record (the transposed reconstruction, and the ell terms,
-        // are applied by the cells that gather it)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            Quad<real> *blk = reinterpret_cast<Quad<real> *>(record_block(J, dir, v, i, j));
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                Quad<real> l, r;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    l.x[c] = gL[v][p][c];
-                    r.x[c] = gR[v][p][c];
-                }
-                blk[p] = l;
-                blk[2 + p] = r;
-            }
+            node_adj<DIR>(A.gamma, A.gtab[kGtabNodeOff + R * 2 + slot], lF, slot, R <= 0 || (R == 2 && k == 1), k < (q >> 1), PL,
+                          PR, gL, gR);
         }
     }
+    // 4. the face's record (the transposed reconstruction, and the ell terms,
+    // are applied by the cells that gather it)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        Quad<real> *blk = reinterpret_cast<Quad<real> *>(record_block(J, DIR, v, i, j));
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            Quad<real> l, r;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                l.x[c] = gL[v][p][c];
+                r.x[c] = gR[v][p][c];
+            }
+            blk[p] = l;
+            blk[2 + p] = r;
+        }
+    }
+}
+
+// One thread per face; blocks below nbx take the x faces, the others the y faces.  Bound
+// by vector instructions and the waits between a position's loads: 10 positions each
+// waited for before the next was read, every corner read also where corners coincide (320
+// loads for 200) and weights loaded by every lane took 115 us at 512^2 in FP32, all cells
+// at the top order; now 78 us (278 -> 185 us in FP64).  The records are 134 MB, 26 us.
+// Three wavefronts a SIMD (two in FP64) spill: the same in FP32, 200 us in FP64.
+template <typename real>
+__global__ __launch_bounds__(128, sizeof(real) == 4 ? 2 : 1) void k_adj_faces(const AdjArgs<real>, int nbx)
+{
+    const AdjArgs<real> &J = first_arg<AdjArgs<real>>();
+    const int b = blockIdx.x;
+    if (b < nbx) face_adj<0>(J, xcd_tile(b, nbx) * 128 + (int)threadIdx.x);
+    else face_adj<1>(J, xcd_tile(b - nbx, gridDim.x - nbx) * 128 + (int)threadIdx.x);
 }
 
 // ------------------------------------------------------------ per-cell gather
@@ -433,12 +528,9 @@ constexpr int kGatherDb[kAdjOffsets] = {0, 0, 0, 1, -1, 0, 0, 2, -2, 1, 1, -1, -
 
 // The contributions to one cell image at window coordinates (bx, by) from the
 // faces of direction DIR, summed over (offset, side) in a fixed order, with the
-// weights of each face's radius from the LDS table (all lanes read the same
-// entries).  TOP: every face of the window has the top radius 3 or does not exist
-// (then its record is zero), so no radius test is needed: the sum has the same
-// bits as the general path's.  CHECK: the image may reach outside the window
-// (ghost images of edge cells).
-template <typename real, int DIR, bool CHECK, bool TOP, int O = 0>
+// weights of each face's radius from the LDS table.  CHECK: the image may reach outside
+// the window (ghost images of edge cells).
+template <typename real, int DIR, bool CHECK, int O = 0>
 __device__ __forceinline__ void gather_sides(const GatherLds<real> &L, int bx, int by, real &sum)
 {
     if constexpr (O < 2 * kAdjOffsets) {
@@ -447,23 +539,46 @@ __device__ __forceinline__ void gather_sides(const GatherLds<real> &L, int bx, i
         constexpr int e = pos_of(iabs_c(da), iabs_c(db));
         const int wx = bx - da + (DIR == 0 && side == 0 ? 1 : 0);
         const int wy = by - db + (DIR == 1 && side == 0 ? 1 : 0);
-        const int f = wy * kWin + wx;
-        const real *g = L.g + f * GatherLds<real>::kStride + side * 8;
-        if constexpr (TOP) {
-            const real *w = L.w + 3 * kGtabPerDir + e * 4;
-            sum += side_term<real, da, db>(*reinterpret_cast<const Quad<real> *>(w),
-                                           *reinterpret_cast<const Quad<real> *>(w + kNPos * 4), g);
-        } else {
-            if (!CHECK || (wx >= 0 && wx < kWin && wy >= 0 && wy < kWin)) {
-                const int R = L.r[f];
-                if (R >= min_radius(e)) {  // not: no face (-1), or beyond its radius
-                    const real *w = L.w + R * kGtabPerDir + e * 4;
-                    sum += side_term<real, da, db>(*reinterpret_cast<const Quad<real> *>(w),
-                                                   *reinterpret_cast<const Quad<real> *>(w + kNPos * 4), g);
-                }
+        const int f0 = (by - 3) * kWin + bx - 3;  // as in gather_top
+        constexpr int df = (3 + (DIR == 1 && side == 0 ? 1 : 0) - db) * kWin + 3 + (DIR == 0 && side == 0 ? 1 : 0) - da;
+        const real *g = L.g + f0 * GatherLds<real>::kStride + df * GatherLds<real>::kStride + side * 8;
+        if (!CHECK || (wx >= 0 && wx < kWin && wy >= 0 && wy < kWin)) {
+            const int R = L.r[f0 + df];
+            if (R >= min_radius(e)) {  // not: no face (-1), or beyond its radius
+                const real *w = L.w + R * kGtabPerDir + e * 4;
+                sum += side_term<real, da, db>(*reinterpret_cast<const Quad<real> *>(w),
+                                               *reinterpret_cast<const Quad<real> *>(w + kNPos * 4), g);
             }
         }
-        gather_sides<real, DIR, CHECK, TOP, O + 1>(L, bx, by, sum);
+        gather_sides<real, DIR, CHECK, O + 1>(L, bx, by, sum);
+    }
+}
+
+// The same sum where every face of the window has the top radius 3 or does not exist
+// (then its record is zero): no radius test is needed, and a position's weights (wt: those
+// of radius 3 and DIR) are uniform and read through the scalar path, not by each lane from
+// LDS, which bounds the gather.  g: the record of the window face (bx - 3, by - 3), from
+// which every offset is positive and so part of the load.
+template <typename real, int DIR, int O = 0>
+__device__ __forceinline__ void gather_top(const real *g, cptr<real> wt, Quad<real> w0, Quad<real> w1, real &sum)
+{
+    if constexpr (O < 2 * kAdjOffsets) {
+        constexpr int o = O / 2, side = O % 2;
+        constexpr int da = kGatherDa[o], db = kGatherDb[o];
+        constexpr int e = pos_of(iabs_c(da), iabs_c(db));
+        constexpr int before = O < 2 ? -1 : pos_of(iabs_c(kGatherDa[(O < 2 ? 2 : O) / 2 - 1]), iabs_c(kGatherDb[(O < 2 ? 2 : O) / 2 - 1]));
+        if constexpr (side == 0 && e != before) {
+            __builtin_amdgcn_sched_barrier(0);  // one position's records at a time
+            wt = reread(wt);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                w0.x[c] = wt[e * 4 + c];
+                w1.x[c] = wt[(kNPos + e) * 4 + c];
+            }
+        }
+        constexpr int dx = 3 + (DIR == 0 && side == 0 ? 1 : 0) - da, dy = 3 + (DIR == 1 && side == 0 ? 1 : 0) - db;
+        sum += side_term<real, da, db>(w0, w1, g + (dy * kWin + dx) * GatherLds<real>::kStride + side * 8);
+        gather_top<real, DIR, O + 1>(g, wt, w0, w1, sum);
     }
 }
 
@@ -532,9 +647,14 @@ __device__ __forceinline__ void fetch_round(const AdjArgs<real> &J, int r, int i
     }
 }
 
+// Bound by LDS reads (each cell reads 25 offsets of both sides, four variables, two
+// directions) and the window's loads (529 faces for 256 cells).  512^2 FP32, all cells at
+// the top order: 95 -> 90 us with the weights off LDS and offsets that are part of the
+// loads (191 -> 133 registers, so three workgroups a CU).
 template <typename real>
-__global__ __launch_bounds__(256, 2) void k_adj_cells(const AdjArgs<real> J)
+__global__ __launch_bounds__(256, sizeof(real) == 4 ? 3 : 2) void k_adj_cells(const AdjArgs<real>)
 {
+    const AdjArgs<real> &J = first_arg<AdjArgs<real>>();
     __shared__ GatherLds<real> L;
     const StageArgs<real> &A = J.A;
     const int nx = A.nx, ny = A.ny;
@@ -608,17 +728,19 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(const AdjArgs<real> J)
             // the cell's own image, then (edge cells of an outflow axis) its ghosts
             real sum = real(0);
             if (top) {
-                if (dir == 0) gather_sides<real, 0, false, true>(L, tx + 3, ty + 3, sum);
-                else gather_sides<real, 1, false, true>(L, tx + 3, ty + 3, sum);
+                const real *g = L.g + (ty * kWin + tx) * KS;
+                const cptr<real> wt = (cptr<real>)A.gtab + 3 * 2 * kGtabPerDir;
+                if (dir == 0) gather_top<real, 0>(g, wt, Quad<real>(), Quad<real>(), sum);
+                else gather_top<real, 1>(g, wt + kGtabPerDir, Quad<real>(), Quad<real>(), sum);
             } else {
-                if (dir == 0) gather_sides<real, 0, false, false>(L, tx + 3, ty + 3, sum);
-                else gather_sides<real, 1, false, false>(L, tx + 3, ty + 3, sum);
+                if (dir == 0) gather_sides<real, 0, false>(L, tx + 3, ty + 3, sum);
+                else gather_sides<real, 1, false>(L, tx + 3, ty + 3, sum);
             }
             for (int qy = 0; qy < niy; ++qy)
                 for (int qx = (qy == 0 ? 1 : 0); qx < nix; ++qx) {
                     const int bx = image(mi, nx, A.bcx, qx) - (i0 - 3), by = image(mj, ny, A.bcy, qy) - (j0 - 3);
-                    if (dir == 0) gather_sides<real, 0, true, false>(L, bx, by, sum);
-                    else gather_sides<real, 1, true, false>(L, bx, by, sum);
+                    if (dir == 0) gather_sides<real, 0, true>(L, bx, by, sum);
+                    else gather_sides<real, 1, true>(L, bx, by, sum);
                 }
             acc[v] += (double)sum;
         }
@@ -654,14 +776,13 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(const AdjArgs<real> J)
 // have the same radius.  An edge cell of an outflow axis also takes the outer
 // side of its boundary face.  Each block sums its cells' terms in a fixed order.
 
-// Parity sums of variable plane U around (ci, cj) (unwrapped) at the kNPos
-// stencil positions, in FP64.
+// The cells of variable plane U at the kNPos stencil positions around (ci, cj)
+// (unwrapped).
 template <typename real>
-__device__ __forceinline__ void parity_sums(const StageArgs<real> &A, const real *U, int ci, int cj,
-                                            double (&q)[kNPos][4])
+__device__ __forceinline__ void corners(const StageArgs<real> &A, const real *U, int ci, int cj, real (&u)[kNPos][4])
 {
     const int nx = A.nx, ny = A.ny;
-    // the seven columns and rows around the centre, then every load, then the sums
+    // the seven columns and rows around the centre, then every load
     int xs[7];
     size_t ys[7];
 #pragma unroll
@@ -669,7 +790,6 @@ __device__ __forceinline__ void parity_sums(const StageArgs<real> &A, const real
         xs[d] = wrap(ci + d - 3, nx, A.bcx);
         ys[d] = (size_t)wrap(cj + d - 3, ny, A.bcy) * nx;
     }
-    real u[kNPos][4];
 #pragma unroll
     for (int e = 0; e < kNPos; ++e) {
         const int a = (int)((kPosA >> (4 * e)) & 15u), b = (int)((kPosB >> (4 * e)) & 15u);
@@ -679,30 +799,65 @@ __device__ __forceinline__ void parity_sums(const StageArgs<real> &A, const real
         u[e][3] = U[ys[3 - b] + xs[3 - a]];
     }
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int e = 0; e < kNPos; ++e)
-        parity4((double)u[e][0], (double)u[e][1], (double)u[e][2], (double)u[e][3], q[e]);
 }
 
-// Sum over the positions e within radius R of dw[p][e][c] q[e][c] g[p][c] (dw:
-// the ell derivatives of the weights of R and the face direction; g: the records
-// of the sides, summed).  TOP: R is the top radius 3.
-template <bool TOP>
-__device__ __forceinline__ double ell_term(const double *dw, const double (&q)[kNPos][4], const double (&g)[2][4],
-                                           int R)
+// The ell terms are formed half of the positions at a time (kHalf), their parity sums in
+// FP64: all ten positions' sums would take 80 registers.
+constexpr int kHalf = kNPos / 2;
+template <typename real>
+__device__ __forceinline__ void parity_half(const real (&u)[kNPos][4], int h, double (&q)[kHalf][4])
 {
-    const int np = TOP ? kNPos : (R <= 0 ? 1 : (R == 1 ? 3 : (R == 2 ? 6 : 10)));
+#pragma unroll
+    for (int e = 0; e < kHalf; ++e) {
+        const real *x = u[h * kHalf + e];
+        parity4((double)x[0], (double)x[1], (double)x[2], (double)x[3], q[e]);
+    }
+}
+
+// sq[p][c]: sums over the positions e within radius R of dw[p][e][c] q[e][c] (dw: the ell
+// derivatives of the weights of R and the face direction), half h added.
+__device__ __forceinline__ void ell_half(const double *dw, int R, int h, const double (&q)[kHalf][4], double (&sq)[2][4])
+{
+    const int np = R <= 0 ? 1 : (R == 1 ? 3 : (R == 2 ? 6 : 10));
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int e = 0; e < kHalf; ++e)
+            if (h * kHalf + e < np) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sq[p][c] = fma(dw[(p * kNPos + h * kHalf + e) * 4 + c], q[e][c], sq[p][c]);
+            }
+}
+
+// The same at the top radius, uniform over the wavefront: the derivatives through the
+// scalar path, 20 (40 scalar registers) at a time.
+__device__ __forceinline__ void ell_half_top(cptr<double> dw, int h, const double (&q)[kHalf][4], double (&sq)[2][4])
+{
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        dw = reread(dw);
+        double w[kHalf][4];
+#pragma unroll
+        for (int e = 0; e < kHalf; ++e)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[e][c] = dw[(p * kNPos + h * kHalf + e) * 4 + c];
+#pragma unroll
+        for (int e = 0; e < kHalf; ++e)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sq[p][c] = fma(w[e][c], q[e][c], sq[p][c]);
+        hold(sq[p]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Sum over p, c of g[p][c] sq[p][c] (g: the records of the sides, summed).
+__device__ __forceinline__ double ell_dot(const double (&g)[2][4], const double (&sq)[2][4])
+{
     double t = 0.0;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double sq = 0.0;
-#pragma unroll
-            for (int e = 0; e < kNPos; ++e)
-                if (e < np) sq = fma(dw[p * (kNPos * 4) + e * 4 + c], q[e][c], sq);
-            t = fma(g[p][c], sq, t);
-        }
+        for (int c = 0; c < 4; ++c) t = fma(g[p][c], sq[p][c], t);
     return t;
 }
 
@@ -721,50 +876,86 @@ __device__ __forceinline__ void add_record(const AdjArgs<real> &J, int dir, int 
     }
 }
 
-// dlw: J.dl64 again, as a restricted pointer the kernel never writes through, so
-// that the block-uniform reads of the top-radius path are scalar loads.
+// Bound by the waits for the records (134 MB at 512^2 in FP32, 28 us) at two wavefronts a
+// SIMD: 50 -> 41 us there, 133 -> 70 us with 2 % of the cells lowered (the weights'
+// derivatives were held in scalar registers across the variables and moved to and from
+// vector lanes).  Three wavefronts a SIMD spill: 297 against 210 us for the whole adjoint.
 template <typename real>
-__global__ __launch_bounds__(256) void k_adj_dl(const AdjArgs<real> J, const double *__restrict__ dlw)
+__global__ __launch_bounds__(256, 2) void k_adj_dl(const AdjArgs<real>)
 {
+    const AdjArgs<real> &J = first_arg<AdjArgs<real>>();
     __shared__ double red[256];
     __shared__ double dwl[4 * 2 * kGtabPerDir];  // the ell derivatives of the weights, [R][dir][.]
-    for (int q = threadIdx.x; q < 4 * 2 * kGtabPerDir; q += blockDim.x) dwl[q] = J.dl64[q];
-    __syncthreads();
     const StageArgs<real> &A = J.A;
     const int nx = A.nx, ny = A.ny;
     const size_t n = (size_t)nx * ny;
     const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     double dl = 0.0;
+    // the radii of the cell's faces (EDP_1: the smaller order of the two cells)
+    int mi = 0, mj = 0, R[2][2] = {{3, 3}, {3, 3}};
     if (k < n) {
-        const int mj = (int)(k / nx), mi = (int)(k - (size_t)mj * nx);
-        // the radii of the cell's faces (EDP_1: the smaller order of the two cells)
+        mj = (int)(k / nx);
+        mi = (int)(k - (size_t)mj * nx);
         const size_t row = (size_t)mj * nx;
         const int o = A.order[k], oxm = A.order[row + wrap(mi - 1, nx, A.bcx)], oxp = A.order[row + wrap(mi + 1, nx, A.bcx)];
         const int oym = A.order[(size_t)wrap(mj - 1, ny, A.bcy) * nx + mi], oyp = A.order[(size_t)wrap(mj + 1, ny, A.bcy) * nx + mi];
-        const int R[2][2] = {{min(oxm, o), min(o, oxp)}, {min(oym, o), min(o, oyp)}};
+        R[0][0] = min(oxm, o);
+        R[0][1] = min(o, oxp);
+        R[1][0] = min(oym, o);
+        R[1][1] = min(o, oyp);
+    }
+    const bool top3 = R[0][0] == 3 && R[0][1] == 3 && R[1][0] == 3 && R[1][1] == 3;
+    const bool edge = (A.bcx != 0 && (mi == 0 || mi == nx - 1)) || (A.bcy != 0 && (mj == 0 || mj == ny - 1));
+    // the table is read from LDS only below the top radius and for the outer sides
+    if (__syncthreads_or(!top3 || edge)) {
+        for (int q = threadIdx.x; q < 4 * 2 * kGtabPerDir; q += blockDim.x) dwl[q] = J.dl64[q];
+        __syncthreads();
+    }
+    if (k < n) {
         // face indices: below (fi, fj) = (mi, mj) in both directions; above, the
         // next index (on a periodic axis the face at the wrap is face 0)
         const int hx = A.bcx == 0 && mi + 1 == nx ? 0 : mi + 1, hy = A.bcy == 0 && mj + 1 == ny ? 0 : mj + 1;
-        const bool top = __all(R[0][0] == 3 && R[0][1] == 3 && R[1][0] == 3 && R[1][1] == 3) != 0;
+        const bool top = __all(top3) != 0;
         for (int v = 0; v < 4; ++v) {
             const real *U = A.Us + (size_t)v * n;
-            double q[kNPos][4];
-            parity_sums(A, U, mi, mj, q);
+            real u[kNPos][4];
+            corners(A, U, mi, mj, u);
+            if (top) {
+                double sq[2][2][4] = {};
 #pragma unroll
-            for (int dir = 0; dir < 2; ++dir) {
-                double g[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-                add_record(J, dir, 1, v, mi, mj, g);  // right side of the face below
-                if (top) {
+                for (int h = 0; h < 2; ++h) {
+                    double q[kHalf][4];
+                    parity_half(u, h, q);
+                    for (int dir = 0; dir < 2; ++dir)
+                        ell_half_top((cptr<double>)J.dl64 + (3 * 2 + dir) * kGtabPerDir, h, q, sq[dir]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int dir = 0; dir < 2; ++dir) {
+                    double g[2][4] = {};
+                    add_record(J, dir, 1, v, mi, mj, g);  // right side of the face below
                     add_record(J, dir, 0, v, dir == 0 ? hx : mi, dir == 0 ? mj : hy, g);
-                    dl += ell_term<true>(dlw + (3 * 2 + dir) * kGtabPerDir, q, g, 3);
-                } else {
-                    const int R0 = R[dir][0], R1 = R[dir][1];
+                    dl += ell_dot(g, sq[dir]);
+                }
+            } else {
+#pragma unroll 1
+                for (int dir = 0; dir < 2; ++dir) {
+                    const int R0 = dir == 0 ? R[0][0] : R[1][0], R1 = dir == 0 ? R[0][1] : R[1][1];
+                    double s0[2][4] = {}, s1[2][4] = {};
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        double q[kHalf][4];
+                        parity_half(u, h, q);
+                        ell_half(dwl + (R0 * 2 + dir) * kGtabPerDir, R0, h, q, s0);
+                        if (R0 != R1) ell_half(dwl + (R1 * 2 + dir) * kGtabPerDir, R1, h, q, s1);
+                    }
+                    double g[2][4] = {}, t[2][4] = {};
+                    add_record(J, dir, 1, v, mi, mj, g);
                     if (R0 == R1) add_record(J, dir, 0, v, dir == 0 ? hx : mi, dir == 0 ? mj : hy, g);
-                    dl += ell_term<false>(dwl + (R0 * 2 + dir) * kGtabPerDir, q, g, R0);
+                    dl += ell_dot(g, s0);
                     if (R0 != R1) {
-                        double h[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-                        add_record(J, dir, 0, v, dir == 0 ? hx : mi, dir == 0 ? mj : hy, h);
-                        dl += ell_term<false>(dwl + (R1 * 2 + dir) * kGtabPerDir, q, h, R1);
+                        add_record(J, dir, 0, v, dir == 0 ? hx : mi, dir == 0 ? mj : hy, t);
+                        dl += ell_dot(t, s1);
                     }
                 }
             }
@@ -775,13 +966,20 @@ __global__ __launch_bounds__(256) void k_adj_dl(const AdjArgs<real> J, const dou
                 const int m = dir == 0 ? mi : mj, nd = dir == 0 ? nx : ny;
                 if ((dir == 0 ? A.bcx : A.bcy) == 0 || m != (hi ? nd - 1 : 0)) continue;
                 const int ci = mi + (dir == 0 ? (hi ? 1 : -1) : 0), cj = mj + (dir == 1 ? (hi ? 1 : -1) : 0);
-                double qg[kNPos][4];
-                parity_sums(A, U, ci, cj, qg);
-                double g[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+                const int Rg = hi ? (dir == 0 ? R[0][1] : R[1][1]) : (dir == 0 ? R[0][0] : R[1][0]);
+                real ug[kNPos][4];
+                corners(A, U, ci, cj, ug);
+                double sg[2][4] = {};
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    double q[kHalf][4];
+                    parity_half(ug, h, q);
+                    ell_half(dwl + (Rg * 2 + dir) * kGtabPerDir, Rg, h, q, sg);
+                }
+                double g[2][4] = {};
                 // the left side of face 0, or the right side of face nd
                 add_record(J, dir, hi ? 1 : 0, v, dir == 0 && hi ? nx : mi, dir == 1 && hi ? ny : mj, g);
-                const int Rg = R[dir][hi];
-                dl += ell_term<false>(dwl + (Rg * 2 + dir) * kGtabPerDir, qg, g, Rg);
+                dl += ell_dot(g, sg);
             }
         }
     }
@@ -816,19 +1014,21 @@ __global__ __launch_bounds__(256) void k_adj_dl_final(const double *partial, int
 }
 
 template <typename real>
-hipError_t launch_stage_vjp(const AdjArgs<real> &J, int nblk_faces, double *dl_out, bool accumulate, hipStream_t st)
+hipError_t launch_stage_vjp(const AdjArgs<real> &J, double *dl_out, bool accumulate, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_adj_faces<real>, dim3(nblk_faces), dim3(128), 0, st, J);
+    const int nx = J.A.nx, ny = J.A.ny;
+    const int nbx = (int)(((size_t)(nx + (J.A.bcx != 0)) * ny + 127) / 128), nby = (int)(((size_t)nx * (ny + (J.A.bcy != 0)) + 127) / 128);
+    hipLaunchKernelGGL(k_adj_faces<real>, dim3((unsigned)(nbx + nby)), dim3(128), 0, st, J, nbx);
     const int tiles = ((J.A.nx + kTile - 1) / kTile) * ((J.A.ny + kTile - 1) / kTile);
     hipLaunchKernelGGL(k_adj_cells<real>, dim3((unsigned)tiles), dim3(kTile * kTile), 0, st, J);
     // one thread per cell: ceil(nx ny / 256) <= tiles blocks, one partial each
     const int nblk_dl = (int)(((size_t)J.A.nx * J.A.ny + 255) / 256);
-    hipLaunchKernelGGL(k_adj_dl<real>, dim3((unsigned)nblk_dl), dim3(256), 0, st, J, J.dl64);
+    hipLaunchKernelGGL(k_adj_dl<real>, dim3((unsigned)nblk_dl), dim3(256), 0, st, J);
     hipLaunchKernelGGL(k_adj_dl_final, dim3(1), dim3(256), 0, st, J.dl_partial, nblk_dl, dl_out, (int)accumulate);
     return hipGetLastError();
 }
 
-template hipError_t launch_stage_vjp<float>(const AdjArgs<float> &, int, double *, bool, hipStream_t);
-template hipError_t launch_stage_vjp<double>(const AdjArgs<double> &, int, double *, bool, hipStream_t);
+template hipError_t launch_stage_vjp<float>(const AdjArgs<float> &, double *, bool, hipStream_t);
+template hipError_t launch_stage_vjp<double>(const AdjArgs<double> &, double *, bool, hipStream_t);
 
 }  // namespace gpm

@@ -267,6 +267,15 @@ __device__ __forceinline__ const T &first_arg()
     return *(const T *)(cptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// Keeps values where they are computed: without it instruction selection moves the
+// products past the next group's weight loads.
+template <int N, typename real>
+__device__ __forceinline__ void hold(real (&x)[N])
+{
+#pragma unroll
+    for (int m = 0; m < N; ++m) asm volatile("" : "+v"(x[m]));
+}
+
 // The four parity sums of the mirror cells pp = (+a,+b), mp = (-a,+b),
 // pm = (+a,-b), mm = (-a,-b), paired along the diagonals so that exchanging the
 // axes (pm <-> mp) leaves EE and OO unchanged and swaps OE and EO bit for bit: a
