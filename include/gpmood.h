@@ -232,8 +232,8 @@ gpm_status gpm_totals_static(gpm_ctx *ctx, const void *U, double totals[4]);
    most tail_threshold troubled cells (0..4096; it hands back to a new batch if a
    pass leaves more than 4 x tail_threshold), with one host check per batch.
    passes_per_check (1..128) is the smallest batch; the batch otherwise follows
-   the previous stage's number of multi-block passes.  rows_per_wave (4..256):
-   rows per wavefront march in the first pass.  Defaults 4, a length chosen from
+   the previous stage's number of multi-block passes (none if it needed none).  rows_per_wave (4..256):
+   rows per wavefront march in the first pass.  Defaults none, a length chosen from
    the grid and the precision (1 to 12 rows: short marches where the grid has too
    few of them to fill the GPU) and 32. */
 gpm_status gpm_set_tuning(gpm_ctx *ctx, int passes_per_check, int rows_per_wave, int tail_threshold);

@@ -103,7 +103,9 @@ gpm_status gpm_create(const gpm_grid *grid, int prec, void *hip_stream, gpm_ctx 
         const double lam = lx > ly ? lx : ly;
         c->slit_lam = lam > c->slit_lam ? lam : c->slit_lam;
     }
-    if (hipHostMalloc((void **)&c->pinned, 64, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void **)&c->pinned, 64, hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&c->pinned_dev, c->pinned, 0) != hipSuccess) {
+        if (c->pinned) (void)hipHostFree(c->pinned);
         delete c;
         return GPM_EHIP;
     }
@@ -384,6 +386,7 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
     C.clist[0] = c->clist[0];
     C.clist[1] = c->clist[1];
     C.ctl = c->ctl;
+    C.report = c->pinned_dev;
     C.tail_thr = c->tail_threshold;
     C.back_thr = 4 * c->tail_threshold;
     PassOut P;
@@ -429,7 +432,6 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
         }
         e = launch_cascade_tail<real>(A, C, k, k + batch, kMaxPasses, c->stream);
         if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("cascade tail: ") + hipGetErrorString(e));
-        HIPCHK(c, hipMemcpyAsync(c->pinned, &c->ctl->tail_end, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         const int tail_end = c->pinned[0], tail_k0 = c->pinned[1], back = c->pinned[2], tail_start = c->pinned[3];
         if (tail_end >= kMaxPasses) {
@@ -444,7 +446,7 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
         if (!back) {
             // multi-block passes this stage needed before the tail (or the end)
             const int head = (tail_k0 > 0 ? tail_k0 : tail_end) - 1;
-            int g = head + 2;
+            int g = head > 0 ? head + 2 : 0;
             g = g < c->passes_per_check ? c->passes_per_check : (g > 128 ? 128 : g);
             c->head_guess = g;
             k = tail_end;

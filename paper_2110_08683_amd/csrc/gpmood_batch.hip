@@ -178,6 +178,7 @@ static gpm_status build_tables(gpm_batch *b)
         C.clist[0] = c->clist[0];
         C.clist[1] = c->clist[1];
         C.ctl = c->ctl;
+        C.report = nullptr;
         // multi-block passes while the previous evaluation left more than
         // tail_threshold troubled cells, then one workgroup per problem to the end
         C.tail_thr = c->tail_threshold;

@@ -88,8 +88,12 @@ struct gpm_ctx {
     double *partial = nullptr;
     void *gtab = nullptr;
     unsigned pass = 0;
-    int passes_per_check = 4;  // smallest batch of multi-block cascade passes
-    int head_guess = 4;        // batch length: the previous stage's multi-block passes + 2
+    // batch length of multi-block cascade passes: the previous stage's number + 2, or none
+    // if it had none (each pass queued in vain costs 3.6 us, a batch too short a hand-back
+    // and another host check, about 30 us; the tail itself takes up to 4 x tail_threshold),
+    // and at least passes_per_check
+    int passes_per_check = 0;
+    int head_guess = 4;
     int tail_threshold = 32;   // troubled cells at or below which one workgroup finishes the cascade
     int rows = 12;             // first-pass march length (march_rows, or gpm_set_tuning)
     int si0 = 0, si1 = 0;  // inflow slit cells [si0, si1)
@@ -97,7 +101,7 @@ struct gpm_ctx {
     double slit_lam = 0.0;  // the slit state's CFL bound (0: none)
     int last_npass = 0;
     bool fresh_ctl = true;
-    int *pinned = nullptr;
+    int *pinned = nullptr, *pinned_dev = nullptr;  // the tail's report: host's and device's address
     // instrumentation
     int instrument = 0;           // bit 0: stage events and iteration counts, bit 1: level statistics
     long long acc_iters = 0, acc_stages = 0;

@@ -901,8 +901,9 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
     const unsigned stamp0 = ctl->stamp0;
     const real dtr = (real)(*A.dt * A.dtf);  // read once, not after each pass's barrier
     load_gtab<tail_threads<real>()>(A.gtab, S.wl);
-    int k0 = ctl->tail_k0 > 0 ? ctl->tail_k0 : kdef;
-    if (ctl->tail_k0 <= 0 && kbeg < kdef) {
+    const int handed = ctl->tail_k0;
+    int k0 = handed > 0 ? handed : kdef;
+    if (handed <= 0 && kbeg < kdef) {
         // no hand-over: the cascade either ended inside the batch kbeg..kdef-1 (at
         // the first pass with no cell) or continues at kdef
         if (threadIdx.x == 0) S.kfirst = kdef;
@@ -972,6 +973,13 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
         }
     }
     if (threadIdx.x == 0) {
+        if (C.report) {
+            // straight into pinned host memory: a copy after the kernel takes 4 us and a gap
+            C.report[0] = k;
+            C.report[1] = handed;
+            C.report[2] = back ? 1 : 0;
+            C.report[3] = k0;
+        }
         ctl->tail_end = k;
         ctl->tail_back = back ? 1 : 0;
         ctl->tail_start = k0;
