@@ -407,8 +407,10 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
         ++c->nev_used;
         HIPCHK(c, hipEventRecord(ev[0], c->stream));
     }
-    // ev[1] is recorded between the first pass and its claims
-    e = launch_first_pass<real>(A, P, C, ev ? ev[1] : nullptr, c->stream);
+    // ev[1] is recorded between the first pass and its claims, which the tail makes where
+    // no multi-block pass goes before it
+    bool tail_claims = c->head_guess == 0;
+    e = launch_first_pass<real>(A, P, C, ev ? ev[1] : nullptr, !tail_claims, c->stream);
     if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("first pass: ") + hipGetErrorString(e));
 
     // Cascade: a batch of multi-block passes (each returns at once when it has no
@@ -430,10 +432,10 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
             e = launch_cascade_pass<real>(A, C, k + b, nb, c->stream);
             if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("cascade pass: ") + hipGetErrorString(e));
         }
-        e = launch_cascade_tail<real>(A, C, k, k + batch, kMaxPasses, c->stream);
+        e = launch_cascade_tail<real>(A, C, tail_claims ? 0 : k, k + batch, kMaxPasses, c->stream);
         if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("cascade tail: ") + hipGetErrorString(e));
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        const int tail_end = c->pinned[0], tail_k0 = c->pinned[1], back = c->pinned[2], tail_start = c->pinned[3];
+        const int tail_end = c->pinned[0], back = c->pinned[1], tail_start = c->pinned[2];
         if (tail_end >= kMaxPasses) {
             c->last_npass = kMaxPasses - 1;
             return fail(c, GPM_ENOTCONV, "MOOD loop exceeded the pass limit");
@@ -444,14 +446,20 @@ static gpm_status run_stage(gpm_ctx *c, const Weights<real> &W, int s, const voi
         c->cstat[1] += tail_end - tail_start;
         c->cstat[2] += back ? 1 : 0;
         if (!back) {
-            // multi-block passes this stage needed before the tail (or the end)
-            const int head = (tail_k0 > 0 ? tail_k0 : tail_end) - 1;
+            // multi-block passes this stage needed
+            const int head = (int)c->cstat[0];
             int g = head > 0 ? head + 2 : 0;
             g = g < c->passes_per_check ? c->passes_per_check : (g > 128 ? 128 : g);
             c->head_guess = g;
             k = tail_end;
             break;
         }
+        if (tail_claims && tail_end == 1) {
+            // too many for the tail: it has not made them
+            e = launch_first_claims<real>(A, P, C, c->stream);
+            if (e != hipSuccess) return fail(c, GPM_EHIP, std::string("claims: ") + hipGetErrorString(e));
+        }
+        tail_claims = false;
         k = tail_end;
         batch = batch < 8 ? 8 : (batch > 64 ? 128 : 2 * batch);
     }

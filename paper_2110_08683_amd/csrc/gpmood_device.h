@@ -123,7 +123,7 @@ struct Cascade {
     int *flist[2];
     int *clist[2];
     Ctl *ctl;
-    int *report;  // host memory for tail_end, tail_k0, tail_back and tail_start (null in a batch)
+    int *report;  // host memory for tail_end, tail_back and tail_start (null in a batch)
     int tail_thr, back_thr;
 };
 

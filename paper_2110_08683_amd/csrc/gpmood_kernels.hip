@@ -874,7 +874,9 @@ __global__ __launch_bounds__(256) void k_cells(const StageArgs<real>, const Casc
 // multi-block passes did not hand over), until a pass has no cell to re-evaluate,
 // kend is reached, or the previous evaluation left more than back_thr troubled
 // cells (hand back to the multi-block passes).  The counts of the running passes
-// stay in LDS and are copied to the control block as each pass completes.
+// stay in LDS and are copied to the control block as each pass completes.  kbeg 0 (then
+// kdef is 1): the claims of the first pass's lowered cells are not made yet; the tail makes
+// them, unless they are more than back_thr (hand back at once).
 // Threads of the tail workgroup: as many as its registers allow (four wavefronts per SIMD
 // in FP32, three in FP64).
 template <typename real>
@@ -903,7 +905,8 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
     load_gtab<tail_threads<real>()>(A.gtab, S.wl);
     const int handed = ctl->tail_k0;
     int k0 = handed > 0 ? handed : kdef;
-    if (handed <= 0 && kbeg < kdef) {
+    const bool claims = kbeg == 0;
+    if (handed <= 0 && !claims && kbeg < kdef) {
         // no hand-over: the cascade either ended inside the batch kbeg..kdef-1 (at
         // the first pass with no cell) or continues at kdef
         if (threadIdx.x == 0) S.kfirst = kdef;
@@ -920,14 +923,33 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
     }
     int k = k0;
     bool back = false;
-    for (; k < kend; ++k) {
+    if (claims) {
+        // a kernel for a few claims costs more than they do (64^2 FP64 step 201 -> 190 us,
+        // RK4 at 200^2 218 -> 211 us)
+        const int nlow = __builtin_amdgcn_readfirstlane(ctl->nlow);
+        if (nlow > C.back_thr) {
+            back = true;
+        } else {
+            __syncthreads();  // the counts are set
+            PassOut P = pass_out(C, 0, stamp0);
+            P.fcount = &S.cnt[k0 & 1][0];
+            P.ccount = &S.cnt[k0 & 1][1];
+            P.tcount = nullptr;  // the first pass has counted them
+            for (int m = (int)threadIdx.x >> 2; __builtin_amdgcn_readfirstlane(m) < nlow; m += tail_threads<real>() / 4) {
+                int i = 0, j = 0;
+                if (m < nlow) split_id(C.clist[0][m], A.nx, A.inv_nx, i, j);
+                claim_after_lowering(A, P, i, j, m < nlow);
+            }
+        }
+    }
+    for (; !back && k < kend; ++k) {
         __syncthreads();  // the previous pass's lists, counts and fluxes are complete
         // the same value in every lane: held in scalar registers, so the branches
         // below (some around block barriers) are scalar
         int nf = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][0]);
         int nc = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][1]);
         const int nt = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][2]);
-        if (threadIdx.x == 0 && k > k0) {
+        if (threadIdx.x == 0 && (claims || k > k0)) {
             ctl->nface[k] = nf;
             ctl->ncell[k] = nc;
             ctl->ntroub[k - 1] = nt;
@@ -976,9 +998,8 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
         if (C.report) {
             // straight into pinned host memory: a copy after the kernel takes 4 us and a gap
             C.report[0] = k;
-            C.report[1] = handed;
-            C.report[2] = back ? 1 : 0;
-            C.report[3] = k0;
+            C.report[1] = back ? 1 : 0;
+            C.report[2] = k0;
         }
         ctl->tail_end = k;
         ctl->tail_back = back ? 1 : 0;
@@ -1602,33 +1623,28 @@ static hipError_t launch_first_pass_rt(const StageArgs<real> &A, const PassOut &
 // which pass 1 only writes after reading its own list C.clist[1]); `mid`, if
 // given, is recorded between the two.
 template <typename real>
-static hipError_t launch_first_pass_and_claims(const StageArgs<real> &A, const PassOut &P, const Cascade &C,
-                                               hipError_t (*fp)(const StageArgs<real> &, const PassOut &, hipStream_t),
-                                               hipEvent_t mid, hipStream_t st)
+hipError_t launch_first_claims(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipStream_t st)
 {
-    PassOut L = P;
-    L.clist = C.clist[0];
-    L.ccount = &C.ctl->nlow;
-    hipError_t e = fp(A, L, st);
-    if (e != hipSuccess) return e;
-    if (mid) {
-        e = hipEventRecord(mid, st);
-        if (e != hipSuccess) return e;
-    }
     hipLaunchKernelGGL(k_claims_first<real>, dim3(256), dim3(256), 0, st, A, P, C.clist[0], &C.ctl->nlow);
     return hipGetLastError();
 }
 
 template <typename real>
-hipError_t launch_first_pass(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipEvent_t mid,
+hipError_t launch_first_pass(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipEvent_t mid, bool claims,
                              hipStream_t st)
 {
+    PassOut Q = P;
+    Q.clist = C.clist[0];
+    Q.ccount = &C.ctl->nlow;
+    hipError_t e;
     switch (A.top) {
-    case 3: return launch_first_pass_and_claims<real>(A, P, C, launch_first_pass_rt<real, 3>, mid, st);
-    case 2: return launch_first_pass_and_claims<real>(A, P, C, launch_first_pass_rt<real, 2>, mid, st);
-    case 1: return launch_first_pass_and_claims<real>(A, P, C, launch_first_pass_rt<real, 1>, mid, st);
+    case 3: e = launch_first_pass_rt<real, 3>(A, Q, st); break;
+    case 2: e = launch_first_pass_rt<real, 2>(A, Q, st); break;
+    case 1: e = launch_first_pass_rt<real, 1>(A, Q, st); break;
     default: return hipErrorInvalidValue;
     }
+    if (e == hipSuccess && mid) e = hipEventRecord(mid, st);
+    return e == hipSuccess && claims ? launch_first_claims<real>(A, P, C, st) : e;
 }
 
 template <typename real>
@@ -1726,10 +1742,12 @@ hipError_t launch_totals(const real *U, size_t ncell, double area, double *parti
     return hipGetLastError();
 }
 
-template hipError_t launch_first_pass<float>(const StageArgs<float> &, const PassOut &, const Cascade &, hipEvent_t,
-                                             hipStream_t);
-template hipError_t launch_first_pass<double>(const StageArgs<double> &, const PassOut &, const Cascade &,
-                                              hipEvent_t, hipStream_t);
+template hipError_t launch_first_pass<float>(const StageArgs<float> &, const PassOut &, const Cascade &, hipEvent_t, bool,
+                                              hipStream_t);
+template hipError_t launch_first_pass<double>(const StageArgs<double> &, const PassOut &, const Cascade &, hipEvent_t, bool,
+                                               hipStream_t);
+template hipError_t launch_first_claims<float>(const StageArgs<float> &, const PassOut &, const Cascade &, hipStream_t);
+template hipError_t launch_first_claims<double>(const StageArgs<double> &, const PassOut &, const Cascade &, hipStream_t);
 template hipError_t launch_cascade_pass<float>(const StageArgs<float> &, const Cascade &, int, int, hipStream_t);
 template hipError_t launch_cascade_pass<double>(const StageArgs<double> &, const Cascade &, int, int, hipStream_t);
 template hipError_t launch_cascade_tail<float>(const StageArgs<float> &, const Cascade &, int, int, int, hipStream_t);

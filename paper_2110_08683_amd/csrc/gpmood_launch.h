@@ -12,7 +12,10 @@ namespace gpm {
 inline int first_pass_waves(int nx, int ny, int rows) { return ((nx + 61) / 62) * ((ny + rows - 1) / rows); }
 
 template <typename real>
-hipError_t launch_first_pass(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipEvent_t mid, hipStream_t st);
+hipError_t launch_first_pass(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipEvent_t mid, bool claims,
+                             hipStream_t st);
+template <typename real>
+hipError_t launch_first_claims(const StageArgs<real> &A, const PassOut &P, const Cascade &C, hipStream_t st);
 template <typename real>
 hipError_t launch_cascade_pass(const StageArgs<real> &A, const Cascade &C, int k, int nblocks, hipStream_t st);
 template <typename real>
