@@ -25,6 +25,7 @@
 // device memory and return at once when it is zero, so passes can be queued
 // without a host round trip.
 #include "gpmood_device.h"
+#include "gpmood_index.h"
 #include "gpmood_launch.h"
 
 namespace gpm {
@@ -796,10 +797,9 @@ __global__ __launch_bounds__(256) void k_claims_first(const StageArgs<real> A, c
     PassOut Q = P;
     Q.stamp = *A.stamp0;
     Q.tcount = nullptr;  // the first pass has counted them
-    const int stride = gridDim.x * blockDim.x;
-    const int nround = (4 * n + stride - 1) / stride;
-    for (int r = 0; r < nround; ++r) {
-        const int t = (r * stride + blockIdx.x * blockDim.x + threadIdx.x) >> 2;
+    const unsigned stride = gridDim.x * blockDim.x, nround = groups_of((unsigned)n, stride / 4);
+    for (unsigned r = 0; r < nround; ++r) {
+        const int t = (int)quad_item(r, stride, blockIdx.x * blockDim.x + threadIdx.x);
         const bool act = t < n;
         int i = 0, j = 0;
         if (act) split_id(low[t], A.nx, A.inv_nx, i, j);
@@ -966,7 +966,7 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
         P.fcount = &S.cnt[(k + 1) & 1][0];
         P.ccount = &S.cnt[(k + 1) & 1][1];
         P.tcount = &S.cnt[(k + 1) & 1][2];
-        const int fw = (8 * nf + 63) >> 6, cw = (4 * nc + 63) >> 6;  // wavefronts of faces, of cells
+        const int fw = (int)groups_of(nf, 8), cw = (int)groups_of(nc, 16);  // wavefronts of faces, of cells
         const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // uniform per wavefront
         if (fw + cw <= tail_threads<real>() / 64) {
             // one round each, on separate wavefronts: the cell wavefronts gather
@@ -1344,7 +1344,7 @@ __global__ __launch_bounds__(256) void k_claims_first_batch(const BatchTabs<real
         PassOut P = table_entry(B.pout, p);
         P.stamp = *A.stamp0;
         P.tcount = nullptr;  // the first pass has counted them
-        const int t = ((w - pl[p]) * 256 + (int)threadIdx.x) >> 2;
+        const int t = (int)quad_item(w - pl[p], 256, threadIdx.x);
         const bool act = t < C.ctl->nlow;
         int i = 0, j = 0;
         if (act) split_id(C.clist[0][t], A.nx, A.inv_nx, i, j);
