@@ -8,7 +8,7 @@
 // terms, u2 per direction), SSP-RK3 (eq. (rk3)), FP64 CFL dt.
 //
 // Kernels:
-//   k3_faces_x, k3_faces_march  the first evaluation at radius 2: every face, a cell's
+//   k3_faces_line, k3_faces_march  the first evaluation at radius 2: every face, a cell's
 //             ball read once for its two faces on the axis (k3_faces_top: radius 1, one
 //             thread per face).
 //   k3_faces  the claimed faces of a cascade pass, one thread per face: both cells' node
@@ -445,7 +445,7 @@ __device__ __forceinline__ void sides3(const Stage3<real> &S, const real (&P)[kN
     for (int n = 0; n < 9; ++n) sp[n][v] = st[n];
 }
 
-// First evaluation at radius 2 (k3_faces_x, k3_faces_march): a cell's ball is read once
+// First evaluation at radius 2 (k3_faces_line, k3_faces_march): a cell's ball is read once
 // for both of its faces on the axis, whose states share the parity entries, and a face
 // takes its left state from the cell one step back.  Bound by vector instructions (about
 // 2300 a cell in FP32) and, at three or four wavefronts a SIMD, the waits between them.
@@ -455,23 +455,34 @@ __device__ __forceinline__ void sides3(const Stage3<real> &S, const real (&P)[kN
 // along y or z by eight columns, which needs no march, took 1000 us: a load of eight short
 // rows takes the cache twice as long as one of 64 cells in a row.
 //
-// On x the cell one step back is the previous lane's: a wavefront runs 64 positions of the
-// rows written one after the other, a ghost cell at either end included, and writes 63
-// faces.
-template <typename real, typename OFF>
-__global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k3_faces_x(const Stage3<real>)
+// k3_faces_line: the cell one step back is the lane `step` below (1 on x, n_x on y, n_x n_y
+// on z): a wavefront runs 64 positions of the lines written one after the other, a ghost cell
+// at either end of each included, and writes 64 - step faces.
+template <typename real, int A, typename OFF>
+__global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k3_faces_line(const Stage3<real>)
 {
     const Stage3<real> &S = first_arg<Stage3<real>>();
+    const int step = A == 0 ? 1 : (A == 1 ? S.n[0] : S.n[0] * S.n[1]);
     int pos[3], loc;
     bool live;
     {
-        const int len = S.n[0] + 2, total = len * S.n[1] * S.n[2], lane = threadIdx.x;
-        const int q = 63 * xcd_tile(blockIdx.x, gridDim.x) + lane, qc = min(q, total - 1), r = qc / len;
-        pos[0] = qc - r * len - 1;  // -1 and n: the ghost cells
-        pos[1] = r % S.n[1];
-        pos[2] = r / S.n[1];
-        live = lane > 0 && pos[0] >= 0 && q < total;
-        loc = r * (S.n[0] + 1) + pos[0];
+        const int len = step * (S.n[A] + 2), lane = threadIdx.x;
+        const int total = len * (A == 0 ? S.n[1] * S.n[2] : (A == 1 ? S.n[2] : 1));
+        const int q = (64 - step) * xcd_tile(blockIdx.x, gridDim.x) + lane, qc = min(q, total - 1), r = qc / len;
+        const int o = qc - r * len, h = o / step, in = o - h * step;
+        if constexpr (A == 0) {
+            pos[1] = r % S.n[1];
+            pos[2] = r / S.n[1];
+        } else if constexpr (A == 1) {
+            pos[0] = in;
+            pos[2] = r;
+        } else {
+            pos[0] = in % S.n[0];
+            pos[1] = in / S.n[0];
+        }
+        pos[A] = h - 1;  // -1 and n: the ghost cells
+        live = lane >= step && pos[A] >= 0 && q < total;
+        loc = (r * (S.n[A] + 1) + pos[A]) * step + in;
     }
     OFF off[25];
     {
@@ -494,27 +505,27 @@ __global__ __launch_bounds__(64, sizeof(real) == 4 ? 4 : 2) void k3_faces_x(cons
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         real P[kNPar3];
-        par3_entries<0>(qn, P);
+        par3_entries<A>(qn, P);
         hold(P);
         if (v < 4) fetch(v + 1, qn);  // in flight during this variable's products
         __builtin_amdgcn_sched_barrier(0);
-        sides3<0>(S, P, v, sm, sp);
+        sides3<A>(S, P, v, sm, sp);
     }
     const Stage3<real> &K = *(const Stage3<real> *)reread((cptr<Stage3<real>>)&S);
     real Fs[5];
     int bad;
-    gauss3<0>(
+    gauss3<A>(
         K, sm,
         [&](int n, real (&sl)[5]) {
 #pragma unroll
-            for (int v = 0; v < 5; ++v) sl[v] = lane_shift<-1>(sp[n][v]);
+            for (int v = 0; v < 5; ++v) sl[v] = A == 0 ? lane_shift<-1>(sp[n][v]) : __shfl_up(sp[n][v], step);
         },
         Fs, bad);
     if (!live) return;
-    const size_t nfa = (size_t)(K.n[0] + 1) * K.n[1] * K.n[2];
+    const size_t nfa = (size_t)(K.n[0] + (A == 0)) * (K.n[1] + (A == 1)) * (K.n[2] + (A == 2));
 #pragma unroll
-    for (int v = 0; v < 5; ++v) K.F[0][v * nfa + loc] = Fs[v];
-    K.Ff[0][loc] = (uint8_t)bad;
+    for (int v = 0; v < 5; ++v) K.F[A][v * nfa + loc] = Fs[v];
+    K.Ff[A][loc] = (uint8_t)bad;
 }
 
 // On y and z a lane marches along the axis over `len` faces, the + states of the cell
@@ -646,10 +657,29 @@ static int march3(const int (&n)[3], int a, long long groups)
     return T;
 }
 
+// On y and z k3_faces_line takes the grids that are thin below the axis: there the march's 64
+// columns lie in many short rows, or are fewer than the lanes, while the line still reads one
+// run of memory and gives up step of its 64 lanes.  Microseconds a smooth step, line against
+// march: FP32 1 x 400 x 400 292 499, 3 x 600 x 600 911 1408, 8 x 350 x 350 799 888,
+// 16 x 256 x 256 854 915, 24 x 200 x 200 781 757, 32 x 200 x 200 1122 1058; FP64 549 752,
+// 1860 2107, 1659 1743, 1737 1764, 1652 1578, 2365 2111.  With few columns FP32 (FP64)
+// 1 x 8 x 4000 174 290 (223 411), 24 x 1 x 4000 259 287 (448 497).
+constexpr int kLineStep = 16, kLineCols = 32;
+
+template <typename real, int A, typename OFF>
+static void launch_line(const Stage3<real> &S, hipStream_t st)
+{
+    const int step = A == 0 ? 1 : (A == 1 ? S.n[0] : S.n[0] * S.n[1]);
+    const long long total = (long long)(S.n[A] + 2) * S.n[(A + 1) % 3] * S.n[(A + 2) % 3];
+    hipLaunchKernelGGL((k3_faces_line<real, A, OFF>), dim3((unsigned)((total - step + 63 - step) / (64 - step))), dim3(64), 0, st,
+                       S);
+}
+
 template <typename real, int A, typename OFF>
 static void launch_march(const Stage3<real> &S, hipStream_t st)
 {
-    const long long groups = ((long long)S.n[0] * S.n[3 - A] + 63) / 64;  // of 64 columns
+    const long long cols = (long long)S.n[0] * S.n[3 - A], groups = (cols + 63) / 64;  // of 64 columns
+    if (S.n[0] * (A == 2 ? S.n[1] : 1) <= kLineStep || cols <= kLineCols) return launch_line<real, A, OFF>(S, st);
     const int len = march3(S.n, A, groups);
     const dim3 g((unsigned)(groups * ((S.n[A] + len) / len)));
     hipLaunchKernelGGL((k3_faces_march<real, A, OFF>), g, dim3(64), 0, st, S, len);
@@ -658,8 +688,7 @@ static void launch_march(const Stage3<real> &S, hipStream_t st)
 template <typename real, typename OFF>
 static void launch_top2(const Stage3<real> &S, hipStream_t st)
 {
-    const long long positions = (long long)(S.n[0] + 2) * S.n[1] * S.n[2];
-    hipLaunchKernelGGL((k3_faces_x<real, OFF>), dim3((unsigned)((positions + 61) / 63)), dim3(64), 0, st, S);
+    launch_line<real, 0, OFF>(S, st);
     launch_march<real, 1, OFF>(S, st);
     launch_march<real, 2, OFF>(S, st);
 }
