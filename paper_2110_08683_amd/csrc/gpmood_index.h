@@ -5,6 +5,10 @@
 
 namespace gpm {
 
+// Faces of an nx x ny grid, x faces and then y faces: on 32768 x 32768 they no longer fit 31
+// bits, so a list holds face ids as unsigned numbers.
+constexpr unsigned faces_of(int nx, int ny) { return (unsigned)(nx + 1) * (unsigned)ny + (unsigned)nx * (unsigned)(ny + 1); }
+
 // Groups of `per` items that hold n items.
 constexpr unsigned groups_of(unsigned n, unsigned per) { return n / per + (n % per != 0u ? 1u : 0u); }
 

@@ -424,19 +424,19 @@ __device__ __forceinline__ bool near_cells(const StageArgs<real> &A, int i, int 
 // count was still unknown; any face id).
 template <bool WALLS, bool HLL, typename real>
 __device__ __forceinline__ void faces_phase(const StageArgs<real> &A, const real *wl, FaceXchg<real> &X,
-                                            const int *flist, int n, int slot, int per, int pre = 0,
+                                            const int *flist, unsigned n, unsigned slot, unsigned per, int pre = 0,
                                             bool use_pre = false)
 {
     const int nx = A.nx, ny = A.ny;
     const int nfx = (nx + 1) * ny, nfy = nx * (ny + 1);
     const size_t plane = (size_t)nx * ny;
     const int lane = threadIdx.x & 63, l8 = lane & 7, oct = lane >> 3, v = lane & 3, side = (lane >> 2) & 1;
-    for (int base = 0; base < n; base += per) {
-        const int idx = base + slot;
-        if (__builtin_amdgcn_readfirstlane(idx) >= n) break;  // nothing (more) for this wavefront
+    for (unsigned base = 0; base < n; base += per) {
+        const unsigned idx = base + slot;
+        if ((unsigned)__builtin_amdgcn_readfirstlane(idx) >= n) break;  // nothing (more) for this wavefront
         const bool valid = idx < n;
-        const int f = (use_pre && base == 0) ? pre : flist[valid ? idx : n - 1];
-        const int dir = f >= nfx ? 1 : 0, fo = dir ? f - nfx : f;
+        const unsigned f = (unsigned)((use_pre && base == 0) ? pre : flist[valid ? idx : n - 1]);
+        const int dir = f >= (unsigned)nfx ? 1 : 0, fo = (int)(dir ? f - (unsigned)nfx : f);
         int i, j;
         split_id(fo, dir ? nx : nx + 1, dir ? A.inv_nx : A.inv_nx1, i, j);
         // this lane's cell: (i, j) on the + side of the face, one step back on the - side
@@ -738,16 +738,16 @@ __device__ __forceinline__ void claim_after_lowering(const StageArgs<real> &A, c
     const unsigned long long any = __ballot(act);
     if (any == 0ull) return;
     const int nx = A.nx, ny = A.ny, lane = threadIdx.x & 63, w = lane & 3;
-    const int nfx = (nx + 1) * ny;
-    const int fx = j * (nx + 1) + i, gy = nfx + j * nx + i;
-    const int fid = w == 0 ? fx : (w == 1 ? fx + 1 : (w == 2 ? gy : gy + nx));
+    const unsigned nfx = (unsigned)((nx + 1) * ny);
+    const unsigned fx = (unsigned)(j * (nx + 1) + i), gy = nfx + (unsigned)(j * nx + i);
+    const unsigned fid = w == 0 ? fx : (w == 1 ? fx + 1 : (w == 2 ? gy : gy + (unsigned)nx));
     const int ii = i + (w == 0 ? -1 : (w == 1 ? 1 : 0)), jj = j + (w == 2 ? -1 : (w == 3 ? 1 : 0));
     const bool cok = (A.bcx == 0 || (ii >= 0 && ii < nx)) && (A.bcy == 0 || (jj >= 0 && jj < ny));
     // (on a non-periodic axis only in-domain indices get here: no mirror needed)
     const int cid = wrap(jj, ny, A.bcy) * nx + wrap(ii, nx, A.bcx);
     // lane 1: the copy of x face 0 / face nx; lane 2: of y face 0 / face ny
     const bool dup = (w == 1 && A.bcx == 0 && (i == 0 || i == nx - 1)) || (w == 2 && A.bcy == 0 && (j == 0 || j == ny - 1));
-    const int did = w == 1 ? j * (nx + 1) + (i == 0 ? nx : 0) : nfx + (j == 0 ? ny * nx : 0) + i;
+    const unsigned did = w == 1 ? (unsigned)(j * (nx + 1) + (i == 0 ? nx : 0)) : nfx + (unsigned)((j == 0 ? ny * nx : 0) + i);
     unsigned a0 = P.stamp, a1 = P.stamp, a2 = P.stamp;
     if (act) {
         a0 = atomicMax(&A.fstamp[fid], P.stamp);
@@ -758,18 +758,19 @@ __device__ __forceinline__ void claim_after_lowering(const StageArgs<real> &A, c
     const bool m0 = a0 < P.stamp, m1 = a1 < P.stamp, m2 = a2 < P.stamp;  // newly claimed here
     const unsigned long long bf0 = __ballot(m0), bc1 = __ballot(m1), bf2 = __ballot(m2 && w != 0), bc2 = __ballot(m2 && w == 0);
     const int nf0 = __popcll(bf0), nc1 = __popcll(bc1);
-    int fb = 0, cb = 0;
+    unsigned fb = 0;
+    int cb = 0;
     if (lane == 0) {
-        fb = atomicAdd(P.fcount, nf0 + __popcll(bf2));
+        fb = (unsigned)atomicAdd(P.fcount, nf0 + __popcll(bf2));
         cb = atomicAdd(P.ccount, nc1 + __popcll(bc2));
         if (P.tcount) atomicAdd(P.tcount, __popcll(any) >> 2);
     }
     fb = __builtin_amdgcn_readfirstlane(fb);
     cb = __builtin_amdgcn_readfirstlane(cb);
-    if (m0) P.flist[fb + below(bf0)] = fid;
+    if (m0) P.flist[fb + (unsigned)below(bf0)] = (int)fid;
     if (m1) P.clist[cb + below(bc1)] = cid;
     if (m2 && w == 0) P.clist[cb + nc1 + below(bc2)] = j * nx + i;
-    if (m2 && w != 0) P.flist[fb + nf0 + below(bf2)] = did;
+    if (m2 && w != 0) P.flist[fb + (unsigned)(nf0 + below(bf2))] = (int)did;
 }
 
 template <bool WALLS, typename real>
@@ -833,20 +834,20 @@ __global__ __launch_bounds__(256) void k_faces(const StageArgs<real>, const Casc
     const StageArgs<real> &A = first_arg<StageArgs<real>>();
     __shared__ real wl[kGtabSize];
     __shared__ FaceXchg<real> xch[4];
-    const int cap = (A.nx + 1) * A.ny + A.nx * (A.ny + 1);
-    const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned cap = faces_of(A.nx, A.ny);
+    const unsigned t0 = blockIdx.x * blockDim.x + threadIdx.x;
     // issued together, before the counts are known: this thread's first list
     // entry (in bounds; used only if the pass runs and covers it) and the weights
-    const int i0 = t0 >> 3;
+    const unsigned i0 = t0 >> 3;
     const int pre = C.flist[k & 1][i0 < cap ? i0 : cap - 1];
     load_gtab<256>(A.gtab, wl);
     if (!pass_runs(C, k)) {
         if (blockIdx.x == 0 && threadIdx.x == 0 && C.ctl->ncell[k] > 0) C.ctl->tail_k0 = k;
         return;
     }
-    int n = C.ctl->nface[k];
+    unsigned n = (unsigned)C.ctl->nface[k];
     n = n < cap ? n : cap;  // a list holds each face at most once
-    if (n <= (int)(blockIdx.x * 32)) return;  // no face for this block
+    if (n <= blockIdx.x * 32) return;  // no face for this block
     __syncthreads();
     faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n, i0, gridDim.x * 32, pre, true);
 }
@@ -898,7 +899,8 @@ template <bool WALLS, bool HLL, typename real>
 __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascade &C, int kbeg, int kdef, int kend,
                                           TailShared<real> &S)
 {
-    const int capf = (A.nx + 1) * A.ny + A.nx * (A.ny + 1), capc = A.nx * A.ny;
+    const unsigned capf = faces_of(A.nx, A.ny);
+    const int capc = A.nx * A.ny;
     Ctl *ctl = C.ctl;
     const unsigned stamp0 = ctl->stamp0;
     const real dtr = (real)(*A.dt * A.dtf);  // read once, not after each pass's barrier
@@ -946,11 +948,11 @@ __device__ __forceinline__ void tail_body(const StageArgs<real> &A, const Cascad
         __syncthreads();  // the previous pass's lists, counts and fluxes are complete
         // the same value in every lane: held in scalar registers, so the branches
         // below (some around block barriers) are scalar
-        int nf = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][0]);
+        unsigned nf = (unsigned)__builtin_amdgcn_readfirstlane(S.cnt[k & 1][0]);
         int nc = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][1]);
         const int nt = __builtin_amdgcn_readfirstlane(S.cnt[k & 1][2]);
         if (threadIdx.x == 0 && (claims || k > k0)) {
-            ctl->nface[k] = nf;
+            ctl->nface[k] = (int)nf;
             ctl->ncell[k] = nc;
             ctl->ntroub[k - 1] = nt;
         }
@@ -1281,10 +1283,10 @@ __device__ __forceinline__ void batch_share(const BatchTabs<real> &B, int p, int
 {
     const StageArgs<real> &A = table_entry(B.args, p);
     const Cascade &C = table_entry(B.casc, p);
-    const int capf = (A.nx + 1) * A.ny + A.nx * (A.ny + 1), capc = A.nx * A.ny;
-    const int nf = C.ctl->nface[k], nc = C.ctl->ncell[k], nt = C.ctl->ntroub[k - 1];  // loaded together
+    const unsigned capf = faces_of(A.nx, A.ny), nf = (unsigned)C.ctl->nface[k];
+    const int capc = A.nx * A.ny, nc = C.ctl->ncell[k], nt = C.ctl->ntroub[k - 1];  // loaded together
     const bool runs = nc > 0 && nt > C.tail_thr;  // pass_runs
-    df = runs ? (min(nf, capf) + 31) / 32 : 0;
+    df = runs ? (int)groups_of(min(nf, capf), 32) : 0;
     dc = runs ? (min(nc, capc) + 63) / 64 : 0;
     if (mark && !runs && nc > 0) C.ctl->tail_k0 = k;  // the tail takes over from this pass
 }
@@ -1403,10 +1405,9 @@ __global__ __launch_bounds__(256) void k_faces_batch(const BatchTabs<real> B, in
             __syncthreads();
             loaded = p;
         }
-        const int capf = (A.nx + 1) * A.ny + A.nx * (A.ny + 1);
-        const int n = min(C.ctl->nface[k], capf);
+        const unsigned n = min((unsigned)C.ctl->nface[k], faces_of(A.nx, A.ny));
         faces_phase<WALLS, HLL>(A, wl, xch[threadIdx.x >> 6], C.flist[k & 1], n,
-                                (w - (PLAN ? first[PLAN ? p : 0] : pl[p])) * 32 + ((int)threadIdx.x >> 3), n);
+                                (unsigned)(w - (PLAN ? first[PLAN ? p : 0] : pl[p])) * 32 + (threadIdx.x >> 3), n);
     }
 }
 

@@ -16,10 +16,11 @@ def index(tmp_path_factory):
     with open(src, "w") as f:
         f.write('#include "gpmood_index.h"\n'
                 'extern "C" unsigned groups(unsigned n, unsigned per) { return gpm::groups_of(n, per); }\n'
-                'extern "C" int item(unsigned r, unsigned threads, unsigned t) { return (int)gpm::quad_item(r, threads, t); }\n')
+                'extern "C" int item(unsigned r, unsigned threads, unsigned t) { return (int)gpm::quad_item(r, threads, t); }\n'
+                'extern "C" unsigned faces(int nx, int ny) { return gpm::faces_of(nx, ny); }\n')
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", CSRC, "-shared", "-fPIC", "-o", out, src])
     L = ctypes.CDLL(out)
-    L.groups.restype = ctypes.c_uint
+    L.groups.restype = L.faces.restype = ctypes.c_uint
     L.item.restype = ctypes.c_int
     return L
 
@@ -40,3 +41,8 @@ def test_claims_cover_every_lowered_cell(index, n, threads):
 @pytest.mark.parametrize("n", [0, 1, 8, 9, 95, 96, 97, (1 << 28) - 1, 1 << 28, 1 << 29, 1 << 30])
 def test_wavefronts_of_a_list(index, n):
     assert index.groups(n, 8) == -(-n // 8) and index.groups(n, 16) == -(-n // 16)
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (62, 5), (32768, 1), (1, 32768), (32767, 32768), (32768, 32768)])
+def test_face_count(index, nx, ny):
+    assert index.faces(nx, ny) == (nx + 1) * ny + nx * (ny + 1)
