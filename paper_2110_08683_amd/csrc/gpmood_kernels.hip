@@ -798,8 +798,8 @@ __global__ __launch_bounds__(256) void k_claims_first(const StageArgs<real> A, c
     PassOut Q = P;
     Q.stamp = *A.stamp0;
     Q.tcount = nullptr;  // the first pass has counted them
-    const unsigned stride = gridDim.x * blockDim.x, nround = groups_of((unsigned)n, stride / 4);
-    for (unsigned r = 0; r < nround; ++r) {
+    const unsigned stride = gridDim.x * blockDim.x;
+    for (unsigned r = 0; quad_item(r, stride, 0) < (unsigned)n; ++r) {
         const int t = (int)quad_item(r, stride, blockIdx.x * blockDim.x + threadIdx.x);
         const bool act = t < n;
         int i = 0, j = 0;
