@@ -231,11 +231,12 @@ gpm_status gpm_totals_static(gpm_ctx *ctx, const void *U, double totals[4]);
    followed by a single-workgroup kernel that finishes it once a pass leaves at
    most tail_threshold troubled cells (0..4096; it hands back to a new batch if a
    pass leaves more than 4 x tail_threshold), with one host check per batch.
-   passes_per_check (1..128) is the smallest batch; the batch otherwise follows
-   the previous stage's number of multi-block passes (none if it needed none).  rows_per_wave (4..256):
-   rows per wavefront march in the first pass.  Defaults none, a length chosen from
-   the grid and the precision (1 to 12 rows: short marches where the grid has too
-   few of them to fill the GPU) and 32. */
+   passes_per_check (0..128) is the smallest batch; the batch otherwise follows
+   the previous stage's number of multi-block passes (none if it needed none).
+   rows_per_wave (0, or 4..256): rows per wavefront march in the first pass; 0: a
+   length chosen from the grid and the precision (1 to 12 rows: short marches where
+   the grid has too few of them to fill the GPU).  Defaults 0, 0 and 32.  Errors:
+   GPM_EINVAL for NULL or a value outside its range. */
 gpm_status gpm_set_tuning(gpm_ctx *ctx, int passes_per_check, int rows_per_wave, int tail_threshold);
 
 /* Instrumentation for measurement (not part of the method).  mode bit 0: every
@@ -339,11 +340,12 @@ gpm_status gpm_batch_workspace_size(const gpm_batch *b, size_t *bytes);
    clears it.  Synchronising.  Errors: GPM_EINVAL for NULL or misalignment. */
 gpm_status gpm_batch_bind(gpm_batch *b, void *mem);
 
-/* First-pass rows per wavefront for every problem (4..256; the default is chosen
-   from the whole batch, as for a single problem). */
+/* First-pass rows per wavefront for every problem (4..256, or 0, the default: a
+   length chosen from the whole batch, as for a single problem). */
 gpm_status gpm_batch_set_tuning(gpm_batch *b, int rows_per_wave);
 
-/* First-pass rows per wavefront of each problem (nprob values, 4..256). */
+/* First-pass rows per wavefront of each problem (nprob values, 4..256, or 0: the
+   length of gpm_batch_set_tuning). */
 gpm_status gpm_batch_set_tuning_per_problem(gpm_batch *b, const int *rows_per_wave);
 
 /* Autotune the first pass's march length (rows per wavefront) per size class of

@@ -397,7 +397,7 @@ class GPMood:
                                             vp(lam_Un.data_ptr() if lam_Un is not None else 0),
                                             vp(dl_dev.data_ptr())))
 
-    def gpm_set_tuning(self, passes_per_check=4, rows_per_wave=12, tail_threshold=32):
+    def gpm_set_tuning(self, passes_per_check=0, rows_per_wave=0, tail_threshold=32):
         self._check(lib().gpm_set_tuning(self.ctx, int(passes_per_check), int(rows_per_wave), int(tail_threshold)))
 
     def gpm_instrument(self, mode=1):
@@ -477,7 +477,7 @@ class GPMoodBatch:
         except Exception:
             pass
 
-    def gpm_batch_set_tuning(self, rows_per_wave=12):
+    def gpm_batch_set_tuning(self, rows_per_wave=0):
         self._check(lib().gpm_batch_set_tuning(self.b, int(rows_per_wave)))
 
     def gpm_batch_set_tuning_per_problem(self, rows):

@@ -40,6 +40,11 @@ const char *gpm_strerror(gpm_status st)
 
 const char *gpm_last_error(const gpm_ctx *ctx) { return ctx ? ctx->err.c_str() : ""; }
 
+static int default_rows(const gpm_ctx *c)
+{
+    return march_rows(c->prec, [&](int T) { return (long long)first_pass_waves(c->nx, c->ny, T); });
+}
+
 gpm_status gpm_create(const gpm_grid *grid, int prec, void *hip_stream, gpm_ctx **out)
 {
     if (!grid || !out) return GPM_EINVAL;
@@ -81,7 +86,7 @@ gpm_status gpm_create(const gpm_grid *grid, int prec, void *hip_stream, gpm_ctx 
     c->nx = grid->n[0];
     c->ny = grid->n[1];
     c->ncell = (size_t)c->nx * c->ny;
-    c->rows = march_rows(prec, [&](int T) { return (long long)first_pass_waves(c->nx, c->ny, T); });
+    c->rows = default_rows(c);
     c->dx = (grid->hi[0] - grid->lo[0]) / c->nx;
     c->dy = (grid->hi[1] - grid->lo[1]) / c->ny;
     c->si0 = si0;
@@ -343,12 +348,12 @@ gpm_status gpm_set_dt(gpm_ctx *c, double dt)
 
 gpm_status gpm_set_tuning(gpm_ctx *c, int passes_per_check, int rows_per_wave, int tail_threshold)
 {
-    if (!c || passes_per_check < 1 || passes_per_check > 128 || rows_per_wave < 4 || rows_per_wave > 256 ||
-        tail_threshold < 0 || tail_threshold > 4096)
+    if (!c || passes_per_check < 0 || passes_per_check > 128 || rows_per_wave < 0 ||
+        (rows_per_wave > 0 && rows_per_wave < 4) || rows_per_wave > 256 || tail_threshold < 0 || tail_threshold > 4096)
         return GPM_EINVAL;
     c->passes_per_check = passes_per_check;
-    c->head_guess = passes_per_check;
-    c->rows = rows_per_wave;
+    c->head_guess = passes_per_check > 0 ? passes_per_check : kHeadStart;
+    c->rows = rows_per_wave > 0 ? rows_per_wave : default_rows(c);
     c->tail_threshold = tail_threshold;
     return GPM_OK;
 }

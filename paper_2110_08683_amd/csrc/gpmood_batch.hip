@@ -40,7 +40,7 @@ struct gpm_batch {
     bool have_scheme = false;
     char *mem = nullptr;
     int rows = 0;               // first-pass rows per wavefront (0: march_rows over the whole batch)
-    std::vector<int> prow;      // first-pass rows per wavefront of each problem (empty: rows)
+    std::vector<int> prow;      // first-pass rows per wavefront of each problem (empty, or an entry of 0: rows)
     int cur = 0;  // slot rotation of the next step (the same for every problem)
     // device tables (inside the caller buffer)
     void *args = nullptr;       // StageArgs<real>[3 rotations][3 stages][nprob]
@@ -114,7 +114,7 @@ static BatchLayout batch_layout(const gpm_batch *b)
     return L;
 }
 
-// The first pass's march length where none was chosen per problem: one pass covers all
+// The first pass's march length where none was chosen for a problem: one pass covers all
 // problems, so their marches fill the chip together.
 static int common_rows(const gpm_batch *b)
 {
@@ -149,7 +149,7 @@ static gpm_status build_tables(gpm_batch *b)
     const int rows = common_rows(b);
     for (int p = 0; p < P; ++p) {
         gpm_ctx *c = b->ctx[p];
-        c->rows = b->prow.empty() ? rows : b->prow[p];
+        c->rows = b->prow.empty() || b->prow[p] == 0 ? rows : b->prow[p];
         const Weights<real> &W = *(const Weights<real> *)(sizeof(real) == 8 ? (const void *)&c->w64 : (const void *)&c->w32);
         for (int r = 0; r < 3; ++r) {
             const int u0 = r, a = (r + 1) % 3, bb = (r + 2) % 3;
@@ -437,7 +437,7 @@ gpm_status gpm_batch_bind(gpm_batch *b, void *mem)
 
 gpm_status gpm_batch_set_tuning(gpm_batch *b, int rows_per_wave)
 {
-    if (!b || rows_per_wave < 4 || rows_per_wave > 256) return GPM_EINVAL;
+    if (!b || rows_per_wave < 0 || (rows_per_wave > 0 && rows_per_wave < 4) || rows_per_wave > 256) return GPM_EINVAL;
     b->rows = rows_per_wave;
     b->prow.clear();
     return rebuild(b);
@@ -447,7 +447,7 @@ gpm_status gpm_batch_set_tuning_per_problem(gpm_batch *b, const int *rows)
 {
     if (!b || !rows) return GPM_EINVAL;
     for (int p = 0; p < b->nprob; ++p)
-        if (rows[p] < 4 || rows[p] > 256) return bfail(b, GPM_EINVAL, "rows per wave must be 4..256");
+        if (rows[p] != 0 && (rows[p] < 4 || rows[p] > 256)) return bfail(b, GPM_EINVAL, "rows per wave must be 0 or 4..256");
     b->prow.assign(rows, rows + b->nprob);
     return rebuild(b);
 }
@@ -486,7 +486,7 @@ gpm_status gpm_batch_autotune(gpm_batch *b, double cfl, int reps, int *rows_out,
                               : launch_batch_dt<float>(tabs<float>(b, b->cur, 0), b->ndt, b->casc, cfl, b->stream);
     BHIPCHK(b, de);
     std::vector<int> rows(P);
-    for (int p = 0; p < P; ++p) rows[p] = b->prow.empty() ? common_rows(b) : b->prow[p];
+    for (int p = 0; p < P; ++p) rows[p] = b->prow.empty() || b->prow[p] == 0 ? common_rows(b) : b->prow[p];
     hipEvent_t e0, e1;
     BHIPCHK(b, hipEventCreate(&e0));
     BHIPCHK(b, hipEventCreate(&e1));

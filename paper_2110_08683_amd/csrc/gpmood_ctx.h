@@ -55,6 +55,8 @@ static inline int march_rows(int prec, Waves waves)
     return best;
 }
 
+constexpr int kHeadStart = 4;  // multi-block cascade passes queued for the first stage
+
 struct gpm_ctx {
     gpm_grid grid;
     int prec;
@@ -93,7 +95,7 @@ struct gpm_ctx {
     // and another host check, about 30 us; the tail itself takes up to 4 x tail_threshold),
     // and at least passes_per_check
     int passes_per_check = 0;
-    int head_guess = 4;
+    int head_guess = kHeadStart;
     int tail_threshold = 32;   // troubled cells at or below which one workgroup finishes the cascade
     int rows = 12;             // first-pass march length (march_rows, or gpm_set_tuning)
     int si0 = 0, si1 = 0;  // inflow slit cells [si0, si1)
