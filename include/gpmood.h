@@ -354,10 +354,11 @@ gpm_status gpm_batch_set_tuning_per_problem(gpm_batch *b, const int *rows_per_wa
    most cells first, each candidate timed on the device with HIP events over reps
    (1..64) launches of the batch's stage-0 first pass, with the dt of the current
    states at this CFL.  Stage 0 reads the current state slot and writes another,
-   so the problems' states are left as they were.  The choice is kept (as
-   gpm_batch_set_tuning_per_problem) and returned in rows_out (nprob values,
-   nullable); gain (nullable) receives the first-pass time of the default march
-   length over the chosen ones.  The march length changes the schedule only:
+   so the problems' states are left as they were.  The choice is returned in
+   rows_out (nprob values, nullable) and kept (as gpm_batch_set_tuning_per_problem)
+   if it is faster than the batch's own length (gpm_batch_set_tuning), which stays
+   otherwise; gain (nullable) receives the first-pass time of that length over the
+   choice's, 1 where the length stays.  The march length changes the schedule only:
    every result is the same bits whatever the choice.  Synchronising.  Errors:
    GPM_EINVAL, GPM_ESTATE (not bound or no scheme), GPM_EHIP. */
 gpm_status gpm_batch_autotune(gpm_batch *b, double cfl, int reps, int *rows_out, double *gain);

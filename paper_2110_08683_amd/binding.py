@@ -486,7 +486,8 @@ class GPMoodBatch:
 
     def gpm_batch_autotune(self, cfl=0.8, reps=3):
         """Run the library's autotuner; returns (rows per problem, first-pass gain
-        of the choice over the default march length)."""
+        of the choice over the default march length, 1 where it is not faster and
+        the default stays)."""
         arr = (ctypes.c_int * self.nprob)()
         gain = ctypes.c_double()
         self._check(lib().gpm_batch_autotune(self.b, float(cfl), int(reps), arr, ctypes.byref(gain)))
@@ -502,7 +503,9 @@ class GPMoodBatch:
     def autotune(self, cfl=0.8, reps=3, cache=None):
         """Autotuned march lengths with an on-disk cache (JSON file `cache`, keyed by
         device, precision, top radius and size class of problem): a batch whose
-        classes are all cached takes the cached choice without timing anything.
+        classes are all cached takes the cached choice without timing anything.  A class
+        whose choice was not faster than the default march length is marked
+        (key + "|default") and keeps the default.
         Returns (rows per problem, gain or None when taken from the cache)."""
         import json
         import os
@@ -515,12 +518,15 @@ class GPMoodBatch:
                 table = json.load(f)
         if all(k in table for k in keys):
             rows = [int(table[k]) for k in keys]
-            self.gpm_batch_set_tuning_per_problem(rows)
+            self.gpm_batch_set_tuning_per_problem([0 if table.get(k + "|default") else r for k, r in zip(keys, rows)])
             return rows, None
         rows, gain = self.gpm_batch_autotune(cfl, reps)
         if cache:
             for k, r in zip(keys, rows):
                 table[k] = r
+                table.pop(k + "|default", None)
+                if gain <= 1.0:
+                    table[k + "|default"] = True
             tmp = cache + ".tmp"
             with open(tmp, "w") as f:
                 json.dump(table, f, indent=1, sort_keys=True)

@@ -458,8 +458,9 @@ gpm_status gpm_batch_set_tuning_per_problem(gpm_batch *b, const int *rows)
 // reads the current slot and writes another, so the timed launches leave the
 // problems' states as they were.  One sweep of coordinate descent, the classes
 // with the most cells first, each over the candidates below; ties keep the
-// shorter march.  The choice changes the schedule only: every stage gives the same
-// bits whatever the march length.
+// shorter march.  Where the choice is not faster than the batch's own length (which on a
+// small batch is below every candidate), that length stays.  The choice changes the schedule
+// only: every stage gives the same bits whatever the march length.
 gpm_status gpm_batch_autotune(gpm_batch *b, double cfl, int reps, int *rows_out, double *gain)
 {
     if (!b || reps < 1 || reps > 64 || !(cfl > 0.0)) return GPM_EINVAL;
@@ -532,9 +533,15 @@ gpm_status gpm_batch_autotune(gpm_batch *b, double cfl, int reps, int *rows_out,
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st != GPM_OK) return st;
+    // a batch too small to fill the GPU is fastest in marches shorter than any candidate
+    const bool faster = ttun < tdef;
+    if (!faster) {
+        b->prow.clear();
+        st = rebuild(b);
+    }
     if (rows_out)
         for (int p = 0; p < P; ++p) rows_out[p] = rows[p];
-    if (gain) *gain = ttun > 0.f ? (double)tdef / (double)ttun : 1.0;
+    if (gain) *gain = faster && ttun > 0.f ? (double)tdef / (double)ttun : 1.0;
     return st;
 }
 
