@@ -232,15 +232,15 @@ __global__ __launch_bounds__(128) void k3_faces(const Stage3<real> S, const int 
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) face3_flux(S, list[t]);
 }
 
-// First evaluation: every face of axis A at the top radius R (every cell starts the
+// First evaluation at top radius 1: every face of axis A (every cell starts the
 // stage at the top order), with the products and sums of face3_flux in the same
 // order.  All 2 x 5 stencils are loaded once into registers; the node loop is
-// rolled and reads each node's 2 x 25 weights through the scalar path (R and A
-// are uniform), so no lane loads a weight.
-template <typename real, int R, int A>
+// rolled and reads each node's 2 x 7 weights through the scalar path (A is
+// uniform), so no lane loads a weight.
+template <typename real, int A>
 __global__ __launch_bounds__(128, 1) void k3_faces_top(const Stage3<real> S)
 {
-    constexpr int ns = R == 1 ? 7 : 25, nq = R == 1 ? 4 : 9;
+    constexpr int ns = 7, nq = 4;
     const int m0 = S.n[0] + (A == 0), m1 = S.n[1] + (A == 1), m2 = S.n[2] + (A == 2);
     const int nfa = m0 * m1 * m2;
     const int loc = blockIdx.x * blockDim.x + threadIdx.x;
@@ -259,9 +259,9 @@ __global__ __launch_bounds__(128, 1) void k3_faces_top(const Stage3<real> S)
             qR[v][m] = S.Us[v * plane + cr];
         }
     }
-    const cptr<real> zL = (cptr<real>)S.z + ((R - 1) * 6 + 2 * A + 1) * 9 * 25;  // + face of the left cell
-    const cptr<real> zR = (cptr<real>)S.z + ((R - 1) * 6 + 2 * A) * 9 * 25;      // - face of the right cell
-    const cptr<real> w = (cptr<real>)S.qw + (R - 1) * 9;
+    const cptr<real> zL = (cptr<real>)S.z + (2 * A + 1) * 9 * 25;  // + face of the left cell
+    const cptr<real> zR = (cptr<real>)S.z + 2 * A * 9 * 25;        // - face of the right cell
+    const cptr<real> w = (cptr<real>)S.qw;
     real Fs[5] = {real(0), real(0), real(0), real(0), real(0)};
     bool bl = false, br = false;
 #pragma unroll 1
@@ -697,16 +697,20 @@ template <typename real, int R>
 static void launch_faces_top(const Stage3<real> &S, hipStream_t st)
 {
     if constexpr (R == 2) {
-        // byte offsets into a variable of 4 GiB or more take 64 bits
-        if ((unsigned long long)S.n[0] * S.n[1] * S.n[2] * sizeof(real) > 0xffffffffull) launch_top2<real, size_t>(S, st);
-        else launch_top2<real, unsigned>(S, st);
+        // byte offsets into a variable of 4 GiB or more take 64 bits: in FP64 only, since face
+        // ids of 31 bits (gpm3_create) end at 699 million cells, 2.8 GB a variable in FP32
+        if constexpr (sizeof(real) == 8) {
+            if ((unsigned long long)S.n[0] * S.n[1] * S.n[2] * sizeof(real) > 0xffffffffull)
+                return launch_top2<real, size_t>(S, st);
+        }
+        launch_top2<real, unsigned>(S, st);
     } else {
         for (int a = 0; a < 3; ++a) {
             const long long nfa = (long long)(S.n[0] + (a == 0)) * (S.n[1] + (a == 1)) * (S.n[2] + (a == 2));
             const dim3 g((unsigned)((nfa + 127) / 128)), t(128);
-            if (a == 0) hipLaunchKernelGGL((k3_faces_top<real, R, 0>), g, t, 0, st, S);
-            if (a == 1) hipLaunchKernelGGL((k3_faces_top<real, R, 1>), g, t, 0, st, S);
-            if (a == 2) hipLaunchKernelGGL((k3_faces_top<real, R, 2>), g, t, 0, st, S);
+            if (a == 0) hipLaunchKernelGGL((k3_faces_top<real, 0>), g, t, 0, st, S);
+            if (a == 1) hipLaunchKernelGGL((k3_faces_top<real, 1>), g, t, 0, st, S);
+            if (a == 2) hipLaunchKernelGGL((k3_faces_top<real, 2>), g, t, 0, st, S);
         }
     }
 }
