@@ -84,7 +84,7 @@ HBM_PEAK = 8.0e12
 # scaled by the counters' reading of a 512 MiB device copy (FETCH x 2.0, WRITE x
 # 1.0).  Valid for the kernel sources with this hash only; see profiles/.
 TRAFFIC = {"src": "77d0b64a68d63acd", "f32": 371.6e6, "f64": 688.1e6}
-KERNEL_SOURCES = ["gpmood_kernels.hip", "gpmood_device.h", "gpmood_tables.h", "gpmood_abi.hip"]
+KERNEL_SOURCES = ["gpmood_kernels.hip", "gpmood_device.h", "gpmood_tables.h", "gpmood_abi.hip", "gpmood_ctx.h"]
 
 
 def kernel_source_hash():

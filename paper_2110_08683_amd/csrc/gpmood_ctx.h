@@ -33,8 +33,12 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // the chip takes short marches, one per SIMD at the least total (64^2 FP64: 12 rows 114
 // us, 1 row 24 us; 512^2: 12 rows 125 us, 3 rows 64 us), and a large one marches far
 // enough that the two extra rows cost little (2048^2 FP64: 4 rows 504 us, 10 rows 478
-// us).  Beyond 12 rows nothing is gained on any size (2048^2 at 24 rows: 502 us FP64,
-// 236 against 210 us FP32).
+// us).  Up to 2048^2 more than 12 rows gain nothing (2048^2 at 24 rows: 484 against 474 us
+// FP64, 230 against 204 us FP32); beyond they gain a little (16 rows: 4096^2 FP64 1718 ->
+// 1670 us, FP32 709 -> 695), and in a batch of 256 problems up to 1024^2, whose marches are
+// many, 3 % (the lengths its autotuner finds).  The row times are those of radius 3; what
+// they choose at radius 1 and 2 is within 7 % of the best of 4 to 32 rows on squares of 64
+// to 6000 cells a side, but for 10 % at 1500^2, radius 1, FP64 (157 against 143 us).
 template <typename Waves>
 static inline int march_rows(int prec, Waves waves)
 {

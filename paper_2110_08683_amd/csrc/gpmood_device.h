@@ -388,10 +388,11 @@ __device__ __forceinline__ void hold4(real (&x)[4])
 }
 
 // Accumulators of all four variables, group by group; ld(v, di, dj).  A group's
-// weights are read once for the four variables and both directions (128 products of
-// the widest group's 16 weights) and given up before the next group's are read: held
-// for a whole row they do not fit the scalar registers, and every product then first
-// fetches its weight from the vector register it was put aside in.
+// weights are read once for the four variables (64 products of the widest group's 16
+// weights; the first pass takes the x faces and the y faces in a call each, and reads
+// them twice) and given up before the next group's are read: held for a whole row they do
+// not fit the scalar registers, and every product then first fetches its weight from the
+// vector register it was put aside in.
 template <int R, bool ISO, int GRP = 0, int D0, int D1, typename real, typename Load>
 __device__ __forceinline__ void accumulate(StateAcc<R, D0, D1, real> (&acc)[4], cptr<real> wt, Load ld)
 {

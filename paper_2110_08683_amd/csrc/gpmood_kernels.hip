@@ -1357,7 +1357,10 @@ __global__ __launch_bounds__(256) void k_claims_first_batch(const BatchTabs<real
 // PLAN: at most 256 problems; every block then lays out the shares itself, one problem a
 // thread, and block 0 writes the cells' for k_cells_batch (a launch of k_batch_plan before
 // each pass took 4.8 us and a gap: 12 FP32 problems of 64^2 to 320^2, 7.07 -> 6.26 ms for six
-// steps).
+// steps).  The line is the block's 256 threads, and it still pays there: a step of problems
+// of 64^2 with the kernel before each pass against this, FP32 (FP64), 12 problems 657 532 us
+// (792 666), 64 892 761 (1069 943), 128 1090 984 (1427 1328), 256 1521 1475 (2148 2113);
+// 256 of 200^2 4486 4438 (7891 7852).
 template <typename real, bool WALLS, bool HLL, bool PLAN>
 __global__ __launch_bounds__(256) void k_faces_batch(const BatchTabs<real> B, int k, int *plan)
 {

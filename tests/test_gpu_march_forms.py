@@ -44,3 +44,27 @@ def test_longer_marches(form, solver, top):
                 ref = ref or got
                 assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(got, ref)), (prec, hi, rows)
                 g.close()
+
+
+# a grid whose automatic length is the longest, 12 rows, in both precisions; the last march
+# of a column runs 4
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_longest_automatic_march(prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2110_08683_amd import GPMood
+    nx, ny = 4000, 700
+    print(f"[gpu-case] longest automatic march {nx}x{ny} {prec}", flush=True)
+    ref = None
+    for rows in (0, 4, 12, 64):
+        g = GPMood(nx, ny, prec=prec, cascade=(3, 2, 1, 0), device="cuda:0")
+        g.gpm_set_tuning(rows_per_wave=rows)
+        U = torch.tensor(gi.noise(nx, ny, seed=2)).to(g.dtype).cuda()
+        g.gpm_compute_dt_dev(U, 0.8)
+        out = torch.empty_like(U)
+        g.gpm_stage_dev(0, U, U, out)
+        got = out.cpu().numpy(), g.gpm_get_order_mask()
+        ref = ref or got
+        assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(got, ref)), rows
+        g.close()
