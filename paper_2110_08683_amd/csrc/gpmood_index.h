@@ -9,8 +9,8 @@ namespace gpm {
 // bits, so a list holds face ids as unsigned numbers.
 constexpr unsigned faces_of(int nx, int ny) { return (unsigned)(nx + 1) * (unsigned)ny + (unsigned)nx * (unsigned)(ny + 1); }
 
-// Groups of `per` items that hold n items.
-constexpr unsigned groups_of(unsigned n, unsigned per) { return n / per + (n % per != 0u ? 1u : 0u); }
+// Groups of `per` items that hold n items (n + per below 2^32: any list of faces or cells).
+constexpr unsigned groups_of(unsigned n, unsigned per) { return (n + (per - 1u)) / per; }
 
 // Four lanes an item: the item of thread t in round r of rounds of `threads` threads.
 // Counted in items, not in lanes: the lanes of 2^29 items no longer fit 31 bits.
